@@ -96,3 +96,29 @@ def test_pool_argument_errors():
     sc3 = sscn.sc_rulebook_build(dev(small_set(371, (9, 9, 9), batch=1)), (9, 9, 9), 3, 2)
     with pytest.raises(sscn.SSCNError):
         sscn.upsample_forward(torch.zeros((sc3.n_out, 4), device="cuda:0"), sc3)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("size,f,s,ch", [((16, 16, 16), 2, 2, 8), ((17, 17, 17), 3, 2, 16), ((16, 16, 16), 2, 2, 96),
+                                         ((18, 18, 18), 6, 6, 40), ((9, 9, 9), 1, 2, 64), ((16, 16, 16), 2, 2, 100)])
+def test_pool_piece_paths(size, f, s, ch, dtype):
+    """Whole 16-byte pieces of 1, 2 and more per row, part piece groups, rows
+    that are whole pieces in fp32 only (100 channels), 1 to 216 offsets."""
+    c = small_set(330 + ch, size, batch=2, density=0.2)
+    _check_pool(c, size, f, s, ch, dtype, 340 + ch)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_average_pool_512_offsets(dtype):
+    """The largest filter (8^3: 128 KB of LDS table), and a tensor whose rows
+    are whole pieces but not 16-byte aligned."""
+    size = (16, 16, 16)
+    c = small_set(350, size, batch=2, density=0.2)
+    rb, orb = sscn.sc_rulebook_build(dev(c), size, 8, 8), O.sc_rulebook(c, size, 8, 8)
+    X = _feat(c.shape[0], 16, 351, dtype)
+    assert_close(host(sscn.pool_forward(dev(X, TD[dtype]), rb, "avg")[0]), O.avg_pool(X, orb), dtype, "AP 8^3")
+    wide = torch.zeros(c.shape[0] * 16 + 2, dtype=TD[dtype], device="cuda")
+    odd = wide[2:].view(c.shape[0], 16)
+    odd.copy_(dev(X, TD[dtype]))
+    assert odd.data_ptr() % 16
+    assert_close(host(sscn.pool_forward(odd, rb, "avg")[0]), O.avg_pool(X, orb), dtype, "AP unaligned")
