@@ -188,6 +188,220 @@ __global__ __launch_bounds__(NW * 64) void k_gather_mma(
   }
 }
 
+// ------------------------------------------- few input channels, one offset
+// 4 consecutive columns of one row to the destinations (fp32 arithmetic, one
+// rounding to T); vec: every destination takes them as one aligned piece.
+template <typename T>
+__device__ __forceinline__ void store4(const Heads<T>& Y, int64_t row, int col, int ncols, bool vec, const float (&a)[4]) {
+  if (!vec || col + 4 > ncols) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (col + i < ncols) Y.store(row, col + i, a[i]);
+    return;
+  }
+  float v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = a[i];
+    if (Y.bias) v[i] += Y.bias[col + i];
+    if (Y.res) v[i] += Elem<T>::load(Y.res + row * Y.res_ld + col + i);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h >= Y.n) break;
+    float q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = Y.scale[h] ? fmaxf(0.f, v[i] * Y.scale[h][col + i] + Y.shift[h][col + i]) : v[i];
+    T* dst = Y.out[h] + row * Y.ld[h] + col;
+    if constexpr (sizeof(T) == 4)
+      *reinterpret_cast<float4*>(dst) = make_float4(q[0], q[1], q[2], q[3]);
+    else
+      *reinterpret_cast<uint2*>(dst) = make_uint2((uint32_t)f32_to_bf16(q[0]) | ((uint32_t)f32_to_bf16(q[1]) << 16),
+                                                  (uint32_t)f32_to_bf16(q[2]) | ((uint32_t)f32_to_bf16(q[3]) << 16));
+  }
+}
+template <typename T>
+__device__ __forceinline__ bool heads_vec4(const Heads<T>& Y) {
+  bool vec = true;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (h < Y.n) vec = vec && reinterpret_cast<uintptr_t>(Y.out[h]) % (4 * sizeof(T)) == 0 && Y.ld[h] % 4 == 0;
+  return vec;
+}
+// The weights of k x ncols (per offset: `rows` reduction channels in all) as
+// fp32 in LDS, columns padded to whole groups of 4: wl[row][4 groups].  TR: W
+// is [o][kdim][ncols], else [o][ncols][kdim].
+template <typename T, bool TR>
+__device__ __forceinline__ void stage_weights(const T* __restrict__ W, int K, int kdim, int ncols, int groups, float* wl) {
+  const int total = K * kdim * groups * 4;
+  for (int i = threadIdx.x; i < total; i += 256) {
+    const int n = i % (groups * 4), k = i / (groups * 4) % kdim, o = i / (groups * 4) / kdim;
+    wl[i] = n < ncols ? Elem<T>::load(W + (TR ? ((int64_t)o * kdim + k) * ncols + n : ((int64_t)o * ncols + n) * kdim + k))
+                      : 0.f;
+  }
+}
+
+// Layers of CI < 8 input channels (a network's first layer on colours or a
+// mere occupancy).  With so few products per pair the matrix cores have
+// nothing to win: a workgroup takes one 64-row tile, writes its pairs into an
+// LDS table (input row by offset and output row, -1 for none), and a thread
+// sums 4 columns of an output row over the offsets in order with fp32
+// multiply-adds, the rows of four offsets in flight.  Bound by instruction
+// issue (about 27 x (3 + 12) loads and multiply-adds a thread at 3 channels).
+// 99,515 sites, 1.14M pairs, 3 -> 32 channels, fp32: 32 us; 251 us on the
+// generic kernel, which walks the tile's pairs 16 at a time through a
+// 64-channel window.
+template <typename T, int CI, bool TR>
+__global__ __launch_bounds__(256) void k_conv_narrow(const T* __restrict__ X, const T* __restrict__ W,
+                                                     const int64_t* __restrict__ seg, int64_t n_tiles,
+                                                     const int32_t* __restrict__ in_rows,
+                                                     const int32_t* __restrict__ out_rows, int K, int mirror, int ncols,
+                                                     int64_t n_out, Heads<T> Y) {
+  extern __shared__ float wl[];
+  const int groups = (ncols + 3) / 4;
+  int32_t* const src = reinterpret_cast<int32_t*>(wl + (size_t)K * CI * groups * 4);  // [o][row]
+  const int64_t t = xcd_remap(blockIdx.x, gridDim.x), row0 = t * kTile;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  stage_weights<T, TR>(W, K, CI, ncols, groups, wl);
+  // a tile holds at most 64 pairs of an offset: one lane per pair; each row of
+  // the table belongs to one wavefront, whose LDS stores keep their order
+  constexpr int U = 4;
+  for (int o0 = wave; o0 < K; o0 += 4 * U) {
+    int64_t p0[U];
+    int n[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = min(o0 + 4 * u, K - 1), so = mirror ? K - 1 - o : o;
+      p0[u] = seg[(int64_t)so * n_tiles + t];
+      n[u] = (int)(seg[(int64_t)so * n_tiles + t + 1] - p0[u]);
+    }
+    int32_t j[U], r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool ok = o0 + 4 * u < K && lane < n[u];
+      j[u] = ok ? in_rows[p0[u] + lane] : -1;
+      r[u] = ok ? (int32_t)(out_rows[p0[u] + lane] - row0) : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (o0 + 4 * u >= K) break;
+      int32_t* dst = src + (o0 + 4 * u) * kTile;
+      dst[lane] = -1;
+      __builtin_amdgcn_wave_barrier();
+      if (j[u] >= 0) dst[r[u]] = j[u];
+    }
+  }
+  __syncthreads();
+  const bool vec = heads_vec4(Y);
+  for (int i = tid; i < kTile * groups; i += 256) {
+    const int r = i / groups, g = i % groups;
+    const int64_t row = row0 + r;
+    if (row >= n_out) break;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < K; o += U) {
+      int32_t j[U];
+      float x[U][CI];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        j[u] = o + u < K ? src[(o + u) * kTile + r] : -1;
+#pragma unroll
+        for (int k = 0; k < CI; ++k) x[u][k] = j[u] >= 0 ? Elem<T>::load(X + (int64_t)j[u] * CI + k) : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (j[u] < 0) continue;
+#pragma unroll
+        for (int k = 0; k < CI; ++k) {
+          const float4 w = *reinterpret_cast<const float4*>(wl + (((o + u) * CI + k) * groups + g) * 4);
+          acc[0] = fmaf(x[u][k], w.x, acc[0]);
+          acc[1] = fmaf(x[u][k], w.y, acc[1]);
+          acc[2] = fmaf(x[u][k], w.z, acc[2]);
+          acc[3] = fmaf(x[u][k], w.w, acc[3]);
+        }
+      }
+    }
+    store4(Y, row, 4 * g, ncols, vec, acc);
+  }
+}
+
+// SSC layers of filter size 1 (every row paired with itself: the per-site
+// linear layer at the end of a network) of at most kPointMax weights: the
+// weights in LDS, a thread sums 4 columns of a row over the kdim channels in
+// order.  Memory-bound, and of less work than a row block costs to set up:
+// 99,515 sites, fp32: 32 -> 20 channels 11 us (16 on the row-block kernel
+// with its weight copy); the gradient, 20 -> 32, 14 us (25 on the column
+// kernel).
+constexpr int kPointMax = 1024;
+template <typename T, bool TR>
+__global__ __launch_bounds__(256) void k_conv_point(const T* __restrict__ X, const T* __restrict__ W, int kdim,
+                                                    int ncols, int64_t n, int64_t rows_per_wg, Heads<T> Y) {
+  extern __shared__ float wl[];
+  const int groups = (ncols + 3) / 4;
+  stage_weights<T, TR>(W, 1, kdim, ncols, groups, wl);
+  __syncthreads();
+  const bool vec = heads_vec4(Y);
+  const int64_t lo = (int64_t)blockIdx.x * rows_per_wg, hi = min<int64_t>(n, lo + rows_per_wg);
+  for (int64_t i = lo * groups + threadIdx.x; i < hi * groups; i += 256) {
+    const int64_t row = i / groups;
+    const int g = (int)(i - row * groups);
+    const T* x = X + row * kdim;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int k = 0; k < kdim; ++k) {
+      const float v = Elem<T>::load(x + k);
+      const float4 w = *reinterpret_cast<const float4*>(wl + (k * groups + g) * 4);
+      acc[0] = fmaf(v, w.x, acc[0]);
+      acc[1] = fmaf(v, w.y, acc[1]);
+      acc[2] = fmaf(v, w.z, acc[2]);
+      acc[3] = fmaf(v, w.w, acc[3]);
+    }
+    store4(Y, row, 4 * g, ncols, vec, acc);
+  }
+}
+
+// Whether a launch (rows of kdim channels in, ncols out) goes to these two
+// kernels: the weights and the tile's table within 48 KB of LDS for fewer than
+// 8 input channels, at most kPointMax weights for filter size 1.
+static bool narrow_eligible(const View& v, int kdim, int ncols) {
+  const size_t lds = sizeof(float) * (size_t)v.K * kdim * ((ncols + 3) / 4 * 4) + sizeof(int32_t) * kTile * (size_t)v.K;
+  return kdim < 8 && lds <= 48 * 1024;
+}
+static bool point_eligible(const View& v, int kdim, int ncols) {
+  return v.K == 1 && v.owner->submanifold && kdim * ncols <= kPointMax;
+}
+template <typename T, bool TR>
+static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim, int ncols, const Heads<T>& Y,
+                                hipStream_t s) {
+  const int groups = (ncols + 3) / 4;
+  size_t lds = sizeof(float) * (size_t)v.K * kdim * groups * 4;
+  if (point_eligible(v, kdim, ncols)) {
+    if (v.n_out == 0) return SSCN_OK;
+    // about four workgroups per CU, at least one pass of 256 threads each
+    const int64_t rows = std::max<int64_t>(ceil_div(256, groups), ceil_div(v.n_out, 1024));
+    k_conv_point<T, TR><<<(unsigned)ceil_div(v.n_out, rows), 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
+    SSCN_HIP(hipGetLastError());
+    return SSCN_OK;
+  }
+  const int64_t tiles = v.st->n_tiles;
+  if (tiles == 0) return SSCN_OK;
+  lds += sizeof(int32_t) * kTile * (size_t)v.K;
+  const auto kern = [&] {
+    switch (kdim) {
+      case 1: return k_conv_narrow<T, 1, TR>;
+      case 2: return k_conv_narrow<T, 2, TR>;
+      case 3: return k_conv_narrow<T, 3, TR>;
+      case 4: return k_conv_narrow<T, 4, TR>;
+      case 5: return k_conv_narrow<T, 5, TR>;
+      case 6: return k_conv_narrow<T, 6, TR>;
+      default: return k_conv_narrow<T, 7, TR>;
+    }
+  }();
+  kern<<<(unsigned)tiles, 256, lds, s>>>(X, W, v.st->seg, tiles, v.st->in_rows, v.st->out_rows, v.K, v.mirror ? 1 : 0,
+                                         ncols, v.n_out, Y);
+  SSCN_HIP(hipGetLastError());
+  return SSCN_OK;
+}
+
 // ------------------------------------------------------------- main path
 // Raw buffer loads: a 32-bit offset from a scalar base, with out-of-range
 // offsets reading as zero (used to mask lanes without branches).
@@ -2141,7 +2355,10 @@ static sscn_status launch_wgrad_reg(bool zeroed, const T* X, const T* dY, const 
     const int64_t target = std::max<int64_t>(1, (int64_t)cus * per_cu / (nzc * nzo));
     // at most target / S tile ranges, so that the items fit one round
     // (a few items left for a second round would double the kernel's time)
-    const int64_t ranges = std::max<int64_t>(1, target / S);
+    // every item adds its block to the same dW elements of its offset with
+    // atomics, which take turns: with few offsets (filter size 1 above all)
+    // at most 256 ranges (32 -> 20 channels at 99,515 sites: 38 -> 22 us)
+    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>(target / S, 256));
     const int64_t tr2 = std::max<int64_t>(1, ceil_div(v.st->n_tiles, ranges));
     const int64_t total = ceil_div(v.st->n_tiles, tr2) * S;
     // deterministic mode: every item block to its own slot, then a
@@ -2510,6 +2727,7 @@ static sscn_status check_conv_args(sscn_rulebook rb, int32_t c_in, int32_t c_out
 // column's reduction channels.
 template <typename T>
 static sscn_status forward_t(const T* X, const T* W, const View& v, int cin, int cout, const Heads<T>& Y, hipStream_t s) {
+  if (narrow_eligible(v, cin, cout) || point_eligible(v, cin, cout)) return launch_small<T, true>(X, W, v, cin, cout, Y, s);
   if (rows_eligible<T>(v, cin, cout)) {
     if (v.n_out == 0) return SSCN_OK;
     if constexpr (sizeof(T) == 4) {
@@ -2661,7 +2879,9 @@ extern "C" sscn_status sparse_conv_backward(const void* features, const void* we
     const View vt = transposed_view(rb);
     if (dtype == SSCN_F32) {
       Heads<float> h = plain_heads((float*)dgrad, c_in);
-      if (rows_eligible<float>(vt, c_out, c_in)) {
+      if (narrow_eligible(vt, c_out, c_in) || point_eligible(vt, c_out, c_in)) {
+        st = launch_small<float, false>((const float*)dout, (const float*)weights, vt, c_out, c_in, h, stream);
+      } else if (rows_eligible<float>(vt, c_out, c_in)) {
         if (wgrad) { h.zero = wgrad; h.n_zero = w_total; w_zeroed = true; }
         if (rows_split(vt, c_out, c_in)) {
           // B[o][ci][co] = W[o][ci][co] as stored, in parts
@@ -2681,7 +2901,9 @@ extern "C" sscn_status sparse_conv_backward(const void* features, const void* we
       }
     } else {
       Heads<bf16_t> h = plain_heads((bf16_t*)dgrad, c_in);
-      if (rows_eligible<bf16_t>(vt, c_out, c_in)) {
+      if (narrow_eligible(vt, c_out, c_in) || point_eligible(vt, c_out, c_in)) {
+        st = launch_small<bf16_t, false>((const bf16_t*)dout, (const bf16_t*)weights, vt, c_out, c_in, h, stream);
+      } else if (rows_eligible<bf16_t>(vt, c_out, c_in)) {
         if (wgrad) { h.zero = wgrad; h.n_zero = w_total; w_zeroed = true; }
         st = launch_rows<bf16_t, true>((const bf16_t*)dout, (const bf16_t*)weights, vt, c_out, c_in, h, stream);
       } else {

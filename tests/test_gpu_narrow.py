@@ -1,0 +1,52 @@
+"""Layers of fewer than 8 input channels and per-site linear layers (filter
+size 1, at most 1024 weights), forward and dgrad, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sscn_oracle as O
+from paper_1711_10275_amd import sscn
+from paper_1711_10275_amd import synthetic as S
+from tests.gpu_common import dev, host, small_set
+from tests.parity import assert_close
+
+pytestmark = pytest.mark.gpu
+
+TD = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def _books(kind, f, s):
+    size = (9, 9, 9) if (f, s) == (3, 2) else (10, 10, 10)
+    c = small_set(7 * f + s, size, batch=2, density=0.2)
+    if kind == "ssc":
+        return sscn.ssc_rulebook_build(dev(c), size, f), O.ssc_rulebook(c, size, f)
+    rb, orb = sscn.sc_rulebook_build(dev(c), size, f, s), O.sc_rulebook(c, size, f, s)
+    return (rb, orb) if kind == "sc" else (rb.transpose(), O.transpose(orb))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind,f,s,cin,cout", [
+    ("ssc", 3, 1, 1, 32), ("ssc", 3, 1, 3, 33), ("ssc", 3, 1, 7, 4), ("ssc", 3, 1, 40, 2), ("ssc", 5, 1, 4, 5),
+    ("sc", 2, 2, 3, 16), ("sc", 3, 2, 6, 130), ("dc", 2, 2, 5, 8), ("ssc", 1, 1, 32, 32), ("ssc", 1, 1, 1, 1),
+    ("ssc", 1, 1, 20, 51), ("ssc", 1, 1, 512, 2), ("ssc", 1, 1, 33, 32)])
+def test_forward_dgrad(kind, f, s, cin, cout, dtype):
+    bf = dtype == "bf16"
+    rb, orb = _books(kind, f, s)
+    X, W = S.features(rb.n_in, cin, 1, bf16=bf), S.weights(rb.n_offsets, cin, cout, 2, bf16=bf)
+    G, bias = S.features(rb.n_out, cout, 3, bf16=bf), S.features(1, cout, 4)[0]
+    t = TD[dtype]
+    want = O.forward(X, W, orb)
+    assert_close(host(sscn.sparse_conv_forward(dev(X, t), dev(W, t), rb)), want, dtype, "forward")
+    # two destinations: a column range at an odd offset, and the plain result with a bias
+    wide = torch.zeros(rb.n_out, cout + 3, dtype=t, device="cuda")
+    plain = torch.empty(rb.n_out, cout, dtype=t, device="cuda")
+    one = torch.ones(cout, device="cuda")
+    sscn.sparse_conv_forward_heads(dev(X, t), dev(W, t), rb, [(wide[:, 1:1 + cout], one, 0 * one), (plain, None, None)],
+                                   bias=dev(bias))
+    assert_close(host(plain), want + bias, dtype, "bias")
+    assert_close(host(wide)[:, 1:1 + cout], np.maximum(0, host(plain)), dtype, "activated")
+    assert not wide[:, 0].any() and not wide[:, 1 + cout:].any()
+    dx, dw = sscn.sparse_conv_backward(dev(X, t), dev(W, t), dev(G, t), rb)
+    rdx, rdw = O.backward(X, W, G, orb)
+    assert_close(host(dx), rdx, dtype, "dgrad")
+    assert_close(host(dw), rdw, "f32", "wgrad")
