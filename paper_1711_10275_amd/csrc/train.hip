@@ -516,59 +516,68 @@ __global__ __launch_bounds__(256) void k_softmax_nll(const T* __restrict__ z, in
 // are added per thread, then per workgroup in thread order.
 constexpr int kSoftmaxRowMax = 64;
 template <typename T>
-__global__ __launch_bounds__(256) void k_softmax_nll_rows(const T* __restrict__ z, int64_t n, int classes,
+__global__ __launch_bounds__(256) void k_softmax_nll_rows(const T* __restrict__ z, int64_t n, int classes, int ldl,
                                                           const int32_t* __restrict__ labels, T* __restrict__ dz,
                                                           double* __restrict__ partial) {
-  __shared__ double red[256];
+  // The workgroup's 256 rows go through LDS (fp32, ldl values apart), loaded
+  // and stored as the consecutive values that they are; a lane on its own row
+  // of global memory touched a line per value (27 us at 99,515 x 20 fp32,
+  // half of it the serial sum of the 256 row losses; now
+  // 16 us).
+  extern __shared__ float rows[];
+  __shared__ double red[4];
   const float inv_n = 1.f / (float)n;
+  const int t = threadIdx.x;
   double acc = 0.0;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-    const T* row = z + r * classes;
-    float m = -INFINITY;
-    for (int k = 0; k < classes; ++k) m = fmaxf(m, ld(row + k));
-    const int lab = labels[r];
-    const bool ok = lab >= 0 && lab < classes;
-    float s = 0.f, so = 0.f;  // as in k_softmax_nll
-    for (int k = 0; k < classes; ++k) {
-      const float e = expf(ld(row + k) - m);
-      s += e;
-      if (k != lab) so += e;
+  for (int64_t r0 = (int64_t)blockIdx.x * 256; r0 < n; r0 += (int64_t)gridDim.x * 256) {
+    const int m_rows = (int)min<int64_t>(256, n - r0), total = m_rows * classes;
+    __syncthreads();
+    for (int i = t; i < total; i += 256) rows[i / classes * ldl + i % classes] = ld(z + r0 * classes + i);
+    __syncthreads();
+    if (t < m_rows) {
+      float* row = rows + t * ldl;
+      float m = -INFINITY;
+      for (int k = 0; k < classes; ++k) m = fmaxf(m, row[k]);
+      const int lab = labels[r0 + t];
+      const bool ok = lab >= 0 && lab < classes;
+      const float zl = ok ? row[lab] : 0.f;
+      float s = 0.f, so = 0.f;  // as in k_softmax_nll
+      for (int k = 0; k < classes; ++k) {
+        const float e = expf(row[k] - m);
+        s += e;
+        if (k != lab) so += e;
+        row[k] = e;
+      }
+      for (int k = 0; k < classes; ++k) row[k] = (k == lab ? -so / s : row[k] / s) * inv_n;
+      double l = (double)NAN;
+      if (ok) {
+        const float el = expf(zl - m);
+        l = el > 0.f ? (double)log1pf(so / el) : (double)(m - zl) + (double)logf(s);
+      }
+      acc += l;
     }
-    for (int k = 0; k < classes; ++k) {
-      const float g = k == lab ? -so / s : expf(ld(row + k) - m) / s;
-      st(dz + r * classes + k, g * inv_n);
-    }
-    double l = (double)NAN;
-    if (ok) {
-      const float zl = ld(row + lab);
-      const float el = expf(zl - m);
-      l = el > 0.f ? (double)log1pf(so / el) : (double)(m - zl) + (double)logf(s);
-    }
-    acc += l;
+    __syncthreads();
+    for (int i = t; i < total; i += 256) st(dz + r0 * classes + i, rows[i / classes * ldl + i % classes]);
   }
-  red[threadIdx.x] = acc;
+  // a fixed tree: reproducible
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
+  if ((t & 63) == 0) red[t >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double sum = 0.0;
-    for (int i = 0; i < (int)blockDim.x; ++i) sum += red[i];
-    partial[blockIdx.x] = sum;
-  }
+  if (t == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// One wavefront: lane l adds blocks l, l + 64, .. in order, then lane 0 adds
-// the 64 lane sums in order.
+// One wavefront: lane l adds blocks l, l + 64, .. in order, then the lanes'
+// sums are added in a fixed tree.
 __global__ __launch_bounds__(64) void k_loss_finalize(const double* __restrict__ partial, int blocks, int64_t n,
                                                       float* __restrict__ loss) {
-  __shared__ double red[64];
   const int l = threadIdx.x;
   double a = 0.0;
+#pragma unroll 8
   for (int b = l; b < blocks; b += 64) a += partial[b];
-  red[l] = a;
-  __syncthreads();
-  if (l != 0) return;
-  double s = 0.0;
-  for (int i = 0; i < 64; ++i) s += red[i];
-  loss[0] = (float)(s / (double)n);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) a += __shfl_xor(a, d, 64);
+  if (l == 0) loss[0] = (float)(a / (double)n);
 }
 
 // g' = g + wd p; buf = momentum buf + g'; p -= lr (g' + momentum buf).
@@ -787,12 +796,14 @@ extern "C" sscn_status sscn_softmax_nll(const void* logits, int64_t n, int32_t c
   Partials part(stream);
   SSCN_TRY(part.alloc(blocks, 1));
   if (per_row) {
+    const int ldl = classes | 1;  // odd: the lanes' rows start in different banks
+    const size_t lds = sizeof(float) * 256 * (size_t)ldl;
     if (dtype == SSCN_F32)
-      k_softmax_nll_rows<float><<<(unsigned)blocks, 256, 0, stream>>>((const float*)logits, n, classes, labels,
-                                                                      (float*)dlogits, part.p);
+      k_softmax_nll_rows<float><<<(unsigned)blocks, 256, lds, stream>>>((const float*)logits, n, classes, ldl, labels,
+                                                                        (float*)dlogits, part.p);
     else
-      k_softmax_nll_rows<uint16_t><<<(unsigned)blocks, 256, 0, stream>>>((const uint16_t*)logits, n, classes, labels,
-                                                                         (uint16_t*)dlogits, part.p);
+      k_softmax_nll_rows<uint16_t><<<(unsigned)blocks, 256, lds, stream>>>((const uint16_t*)logits, n, classes, ldl,
+                                                                           labels, (uint16_t*)dlogits, part.p);
   } else if (dtype == SSCN_F32)
     k_softmax_nll<float><<<(unsigned)blocks, 256, 0, stream>>>((const float*)logits, n, classes, labels,
                                                                (float*)dlogits, part.p);
