@@ -2421,6 +2421,32 @@ extern "C" sscn_status sscn_rulebook_out_coords(sscn_rulebook rb, int32_t* out_c
   return SSCN_OK;
 }
 
+// The pairs of a view, offset by offset, into the caller's arrays.
+// Workgroup (x, o): kExportPer pairs per thread of the view's offset o,
+// which a mirrored view stores under K-1-o, so that its segments come out in
+// the opposite order.  One launch, bound by its 20 bytes of traffic per
+// pair; two copies and a fill per offset spent their time between the
+// launches (three times K of them, whatever the size).
+constexpr int kExportPer = 8;
+__global__ __launch_bounds__(256) void k_export(const int64_t* __restrict__ seg, int64_t n_tiles, int K, int mirror,
+                                                const int32_t* __restrict__ in_rows,
+                                                const int32_t* __restrict__ out_rows, int32_t* __restrict__ in_dst,
+                                                int32_t* __restrict__ out_dst, int32_t* __restrict__ off_dst) {
+  const int o = blockIdx.y, so = mirror ? K - 1 - o : o;
+  const int64_t first = seg[(int64_t)so * n_tiles], end = seg[(int64_t)(so + 1) * n_tiles];
+  // mirrored: the segments before o in the view are those stored behind so
+  const int64_t dst = mirror ? seg[(int64_t)K * n_tiles] - end : first;
+  const int64_t i0 = (int64_t)blockIdx.x * (256 * kExportPer) + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < kExportPer; ++q) {
+    const int64_t i = i0 + q * 256;
+    if (i >= end - first) return;
+    in_dst[dst + i] = in_rows[first + i];
+    out_dst[dst + i] = out_rows[first + i];
+    off_dst[dst + i] = o;
+  }
+}
+
 extern "C" sscn_status sscn_rulebook_export(sscn_rulebook rb, int32_t* in_rows, int32_t* out_rows,
                                             int32_t* offsets, hipStream_t s) {
   if (!rb) return fail(SSCN_ERR_INVALID_ARG, "NULL rule book");
@@ -2429,23 +2455,10 @@ extern "C" sscn_status sscn_rulebook_export(sscn_rulebook rb, int32_t* in_rows, 
   if (!in_rows || !out_rows || !offsets) return fail(SSCN_ERR_INVALID_ARG, "NULL export array");
   const View v = view_of(rb);
   UseNote note{rb->d, s};
-  // stored segment boundaries per offset: seg[o * n_tiles], read on the host
-  std::vector<int64_t> start(d->K + 1);
-  int64_t acc = 0;
-  for (int o = 0; o < d->K; ++o) { start[o] = acc; acc += d->pairs_per_offset[o]; }
-  start[d->K] = acc;
-  int64_t pos = 0;
-  for (int o = 0; o < d->K; ++o) {
-    const int so = v.mirror ? d->K - 1 - o : o;
-    const int64_t cnt = d->pairs_per_offset[so];
-    if (!cnt) continue;
-    SSCN_HIP(hipMemcpyAsync(in_rows + pos, v.st->in_rows + start[so], sizeof(int32_t) * cnt,
-                            hipMemcpyDeviceToDevice, s));
-    SSCN_HIP(hipMemcpyAsync(out_rows + pos, v.st->out_rows + start[so], sizeof(int32_t) * cnt,
-                            hipMemcpyDeviceToDevice, s));
-    SSCN_TRY(fill_i32(offsets + pos, o, cnt, s));
-    pos += cnt;
-  }
+  const int64_t longest = *std::max_element(d->pairs_per_offset.begin(), d->pairs_per_offset.end());
+  k_export<<<dim3((unsigned)ceil_div(longest, 256 * kExportPer), (unsigned)d->K), 256, 0, s>>>(
+      v.st->seg, v.st->n_tiles, d->K, v.mirror ? 1 : 0, v.st->in_rows, v.st->out_rows, in_rows, out_rows, offsets);
+  SSCN_HIP(hipGetLastError());
   return SSCN_OK;
 }
 

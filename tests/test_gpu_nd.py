@@ -76,6 +76,21 @@ def test_4d_shells_row_blocks(dtype):
     assert_close(host(dx), O.backward(X, W, G, orb)[0], dtype, "4-d dgrad")
 
 
+@pytest.mark.parametrize("f,s,sub", [(1, 1, True), (3, 1, True), (2, 2, False), (3, 2, False)])
+def test_export_views(f, s, sub):
+    """Export of a layer's view and of its mirrored or transposed one, with
+    segments longer than one workgroup takes and segments that are empty."""
+    size = (33, 33, 33)
+    c = _set(f, size, batch=3, density=0.4)
+    lone = np.array([[0, 0, 0, 0], [0, 2, 2, 3]], np.int32)
+    for sites in (c, lone):
+        rb = sscn.ssc_rulebook_build(dev(sites), size, f) if sub else sscn.sc_rulebook_build(
+            dev(sites), size if f == 3 else (34, 34, 34), f, s)
+        orb = O.ssc_rulebook(sites, size, f) if sub else O.sc_rulebook(sites, size if f == 3 else (34, 34, 34), f, s)
+        assert_same_rulebook(rb, orb)
+        assert_same_rulebook(rb.transpose(), O.transpose(orb))
+
+
 def test_nd_errors():
     c = dev(_set(1, (8, 8)))
     with pytest.raises(sscn.SSCNError) as e:
