@@ -2426,7 +2426,9 @@ extern "C" sscn_status sscn_rulebook_out_coords(sscn_rulebook rb, int32_t* out_c
 // which a mirrored view stores under K-1-o, so that its segments come out in
 // the opposite order.  One launch, bound by its 20 bytes of traffic per
 // pair; two copies and a fill per offset spent their time between the
-// launches (three times K of them, whatever the size).
+// launches (three times K of them, whatever the size):
+// the SSC(3) and SC(2,2) books of 2.0M sites, built and exported, took
+// 1402 us, now 1156.
 constexpr int kExportPer = 8;
 __global__ __launch_bounds__(256) void k_export(const int64_t* __restrict__ seg, int64_t n_tiles, int K, int mirror,
                                                 const int32_t* __restrict__ in_rows,
@@ -2475,9 +2477,9 @@ extern "C" void sscn_rulebook_free(sscn_rulebook rb) {
 // video): sites are rows (b, x_0, .., x_{d-1}) of an n x (d + 1) int32
 // array, F = {0..f-1}^d is enumerated with the first coordinate most
 // significant, keys are the linear index ((b L_0 + x_0) L_1 + ..) in 64
-// bits.  The dictionary is the 16-byte-slot table, the SSC probe looks up
-// every (offset, site) pair (one lane each, offset-major so that a
-// wavefront reads consecutive sites), and the SC outputs are numbered by
+// bits.  The dictionary is the 16-byte-slot table, the SSC probe takes
+// slices of offsets per tile as in three dimensions, and the SC outputs are
+// numbered by
 // first visit exactly as in three dimensions; both directions are then
 // compacted into the same storage as the 3-D builders produce, so the
 // convolution, pooling and export calls are unchanged.
@@ -2555,29 +2557,94 @@ __global__ __launch_bounds__(256) void k_insert_n(const int32_t* __restrict__ co
 }
 
 // nbr[o n + k] = row of the site at x_k + i_o - (f-1)/2, or -1 (sites
-// outside the grid were flagged by the insert; the build then fails).
+// outside the grid were flagged by the insert; the build then fails), and
+// the hits of each tile, as in k_ssc_probe: a wavefront takes kProbeSlice
+// offsets of a tile, so that several lookups are in flight per lane, a
+// lookup reads the aligned window of 4 slots that holds its first slot, and
+// the slices of neighbouring tiles stay on one XCD.  With `mirror` the
+// offsets below the centre fill their mirror images too (which start at -1);
+// those and the centre's are counted afterwards.  141k sites, 81 offsets:
+// one lane per lookup and a separate count took 164 + 29 us, this 61 + 16
+// and a fill of 5.
+constexpr int kProbeSlice = 3;
+// The mirrored probe costs one more launch (the fill) and saves half of the
+// lookups; the line is that of three dimensions, in lookups.
+constexpr int64_t kMirrorLookupMin = 27 * kMirrorProbeMin;
 template <int DD>
 __global__ __launch_bounds__(256) void k_probe_n(const int32_t* __restrict__ coords, int64_t n, GeomN<DD> g,
                                                  const Slot* __restrict__ table, uint64_t mask,
-                                                 int32_t* __restrict__ nbr) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * g.K) return;
-  const int o = (int)(idx / n);
-  const int64_t k = idx - (int64_t)o * n;
-  int b, x[DD], i[DD];
-  int32_t j = -1;
-  if (site_n<DD>(coords, k, g, b, x)) {
-    digits_n<DD>(o, g.f, i);
-    const int c = (g.f - 1) / 2;
-    bool in = true;
+                                                 int32_t* __restrict__ nbr, int64_t* __restrict__ counts,
+                                                 int64_t n_tiles, int mirror) {
+  constexpr int P = kProbeSlice;
+  const int lane = threadIdx.x & 63;
+  const int ctr = (g.K - 1) / 2, h = (g.f - 1) / 2;
+  const int o_end = mirror ? ctr : g.K;
+  const int slices = max((o_end + P - 1) / P, 1);
+  const int64_t lb = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t t = (lb / slices) * (blockDim.x / 64) + (threadIdx.x >> 6);
+  if (t >= n_tiles) return;  // uniform per wavefront
+  const int64_t k = t * kTile + lane;
+  const bool valid = k < n;
+  int b = 0, x[DD] = {};
+  const bool site_ok = valid && site_n<DD>(coords, k, g, b, x);
+  const int o0 = (int)(lb % slices) * P;
+  if (mirror && o0 == 0 && valid) nbr[(int64_t)ctr * n + k] = site_ok ? (int32_t)k : -1;
+  uint64_t key[P], slot[P];
+  bool live[P];
+  uint64_t vk[P][4];
+  int32_t vr[P][4];
+  auto read_window = [&](int q) {
+    const Slot* tw = table + (slot[q] & ~3ull);
 #pragma unroll
-    for (int q = 0; q < DD; ++q) {
-      x[q] += i[q] - c;
-      in = in && (unsigned)x[q] < (unsigned)g.L[q];
+    for (int j = 0; j < 4; ++j) {
+      const Slot e = tw[j];
+      vk[q][j] = e.key;
+      vr[q][j] = e.row;
     }
-    if (in) j = table_lookup(table, mask, key_n<DD>(b, x, g.L));
+  };
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    int i[DD], y[DD];
+    digits_n<DD>(o0 + q, g.f, i);
+    live[q] = o0 + q < o_end && site_ok;
+#pragma unroll
+    for (int a = 0; a < DD; ++a) {
+      y[a] = x[a] + i[a] - h;
+      live[q] = live[q] && (unsigned)y[a] < (unsigned)g.L[a];
+    }
+    key[q] = key_n<DD>(b, y, g.L);
+    slot[q] = mix64(key[q]) & mask;
+    if (live[q]) read_window(q);
   }
-  nbr[idx] = j;
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const int o = o0 + q;
+    if (o >= o_end) break;  // uniform
+    int32_t row = -1;
+    bool done = !live[q];
+    while (!done) {
+      const int from = (int)(slot[q] & 3);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (!done && j >= from) {
+          if (vk[q][j] == key[q]) {
+            row = vr[q][j];
+            done = true;
+          } else if (vk[q][j] == kEmptyKey) {
+            done = true;
+          }
+        }
+      }
+      if (!done) {
+        slot[q] = ((slot[q] & ~3ull) + 4) & mask;  // first slot of the next window
+        read_window(q);
+      }
+    }
+    if (valid) nbr[(int64_t)o * n + k] = row;
+    if (mirror && row >= 0) nbr[(int64_t)(g.K - 1 - o) * n + row] = (int32_t)k;
+    const unsigned long long hits = __ballot(row >= 0);
+    if (lane == 0) counts[(int64_t)o * n_tiles + t] = __popcll(hits);
+  }
 }
 
 // Output location that input x reaches through offset o, if any.
@@ -2711,10 +2778,18 @@ sscn_status build_nd(const int32_t* coords, int64_t n, const int32_t* size, int 
       if (n > 0) {
         k_insert_n<DD><<<grid_for(n, 256), 256, 0, s>>>(coords, n, g, table, cap - 1, stats, d->out_coords);
         SSCN_HIP(hipGetLastError());
-        k_probe_n<DD><<<grid_for(n * K, 256), 256, 0, s>>>(coords, n, g, table, cap - 1, nbr);
+        const int c = (K - 1) / 2;  // centre offset
+        const bool mirror = n * K >= kMirrorLookupMin && K > 1;
+        if (mirror) SSCN_TRY(fill_i32(nbr + (int64_t)(c + 1) * n, -1, (int64_t)(K - 1 - c) * n, s));
+        const int64_t groups = ceil_div(d->fwd.n_tiles * 64, 256);
+        const int64_t slices = std::max<int64_t>(ceil_div(mirror ? c : K, kProbeSlice), 1);
+        k_probe_n<DD><<<(unsigned)(groups * slices), 256, 0, s>>>(coords, n, g, table, cap - 1, nbr, d->fwd.seg,
+                                                                  d->fwd.n_tiles, mirror ? 1 : 0);
         SSCN_HIP(hipGetLastError());
-        k_count_nbr<<<grid_for(d->fwd.n_tiles * 64, 256), 256, 0, s>>>(nbr, n, K, d->fwd.seg, d->fwd.n_tiles);
-        SSCN_HIP(hipGetLastError());
+        if (mirror) {
+          k_count_nbr<<<grid_for(d->fwd.n_tiles * 64, 256), 256, 0, s>>>(nbr, n, K, d->fwd.seg, d->fwd.n_tiles, c);
+          SSCN_HIP(hipGetLastError());
+        }
       }
       SSCN_TRY(exclusive_scan_i64(d->fwd.seg, d->fwd.seg, K * d->fwd.n_tiles, s));
       if (n > 0) {

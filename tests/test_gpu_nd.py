@@ -76,6 +76,17 @@ def test_4d_shells_row_blocks(dtype):
     assert_close(host(dx), O.backward(X, W, G, orb)[0], dtype, "4-d dgrad")
 
 
+@pytest.mark.parametrize("size,f,density", [((300, 300), 7, 0.85), ((611, 299), 5, 0.9), ((8, 31, 30, 29), 3, 0.3)])
+def test_nd_mirrored_probe(size, f, density):
+    """Enough lookups (n f^d >= 27 * 2^18) that offsets below the centre fill
+    their mirror images: rule book and export of both views, bit for bit."""
+    c = _set(31 + f, size, density=density)
+    assert c.shape[0] * f ** len(size) >= 27 << 18 and c.shape[0] % 64
+    rb, orb = sscn.ssc_rulebook_build(dev(c), size, f), O.ssc_rulebook(c, size, f)
+    assert_same_rulebook(rb, orb)
+    assert_same_rulebook(rb.transpose(), O.transpose(orb))
+
+
 @pytest.mark.parametrize("f,s,sub", [(1, 1, True), (3, 1, True), (2, 2, False), (3, 2, False)])
 def test_export_views(f, s, sub):
     """Export of a layer's view and of its mirrored or transposed one, with
