@@ -367,7 +367,7 @@ static bool narrow_eligible(const View& v, int kdim, int ncols) {
   return kdim < 8 && lds <= 48 * 1024;
 }
 static bool point_eligible(const View& v, int kdim, int ncols) {
-  return v.K == 1 && v.owner->submanifold && kdim * ncols <= kPointMax;
+  return v.K == 1 && v.owner->submanifold && (int64_t)kdim * ncols <= kPointMax;
 }
 template <typename T, bool TR>
 static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim, int ncols, const Heads<T>& Y,
