@@ -369,6 +369,18 @@ static bool narrow_eligible(const View& v, int kdim, int ncols) {
 static bool point_eligible(const View& v, int kdim, int ncols) {
   return v.K == 1 && v.owner->submanifold && (int64_t)kdim * ncols <= kPointMax;
 }
+template <typename T>
+static bool rows_eligible(const View& v, int kdim, int ncols);
+template <typename T>
+static bool prefer_col(const View& v, int cin, int cout);
+// The table that the general kernels would use for this layer: any forward or
+// backward call leaves it behind for the no-allocation forward, whose layers
+// may be wider ones on the same rule book, and which is refused without it.
+template <typename T>
+static sscn_status ensure_general_table(const View& v, int kdim, int ncols, hipStream_t s) {
+  if (rows_eligible<T>(v, kdim, ncols)) return ensure_plan(v, s);
+  return prefer_col<T>(v, kdim, ncols) ? ensure_chunks(v, s) : SSCN_OK;
+}
 template <typename T, bool TR>
 static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim, int ncols, const Heads<T>& Y,
                                 hipStream_t s) {
@@ -376,6 +388,7 @@ static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim,
   size_t lds = sizeof(float) * (size_t)v.K * kdim * groups * 4;
   if (point_eligible(v, kdim, ncols)) {
     if (v.n_out == 0) return SSCN_OK;
+    SSCN_TRY(ensure_general_table<T>(v, kdim, ncols, s));
     // about four workgroups per CU, at least one pass of 256 threads each
     const int64_t rows = std::max<int64_t>(ceil_div(256, groups), ceil_div(v.n_out, 1024));
     k_conv_point<T, TR><<<(unsigned)ceil_div(v.n_out, rows), 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
@@ -384,6 +397,7 @@ static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim,
   }
   const int64_t tiles = v.st->n_tiles;
   if (tiles == 0) return SSCN_OK;
+  SSCN_TRY(ensure_general_table<T>(v, kdim, ncols, s));
   lds += sizeof(int32_t) * kTile * (size_t)v.K;
   const auto kern = [&] {
     switch (kdim) {

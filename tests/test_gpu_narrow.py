@@ -1,5 +1,7 @@
 """Layers of fewer than 8 input channels and per-site linear layers (filter
 size 1, at most 1024 weights), forward and dgrad, against the CPU oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -50,3 +52,28 @@ def test_forward_dgrad(kind, f, s, cin, cout, dtype):
     rdx, rdw = O.backward(X, W, G, orb)
     assert_close(host(dx), rdx, dtype, "dgrad")
     assert_close(host(dw), rdw, "f32", "wgrad")
+
+
+@pytest.mark.parametrize("dim,f,cin,cout", [(4, 1, 32, 20), (3, 3, 4, 16), (4, 1, 20, 32)])
+def test_tables_for_the_no_allocation_forward(dim, f, cin, cout):
+    """One ordinary call leaves the tables that a wider layer of the same kind
+    needs in a no-allocation forward; without it that layer is refused."""
+    size = (8,) * dim
+    c = np.concatenate([np.zeros((40, 1), np.int32), np.random.default_rng(5).permutation(
+        np.stack(np.meshgrid(*[np.arange(8)] * dim, indexing="ij"), -1).reshape(-1, dim))[:40].astype(np.int32)], 1)
+    rb = sscn.ssc_rulebook_build(dev(c), size, f)
+
+    def noalloc(ci, co):
+        X, W = dev(S.features(40, ci, 1)), dev(S.weights(f ** dim, ci, co, 2))
+        out = torch.empty(40, co, device="cuda")
+        p, code = ctypes.c_void_p, sscn.lib().sparse_conv_forward_noalloc
+        st = code(p(X.data_ptr()), p(W.data_ptr()), rb.handle, ci, co, sscn.F32, p(out.data_ptr()),
+                  p(torch.cuda.current_stream().cuda_stream))
+        return st, lambda: torch.equal(out, sscn.sparse_conv_forward(X, W, rb))
+
+    wide = 4 * (16 if cin % 8 == 0 else 17)
+    assert noalloc(cin, cout)[0] != 0 and noalloc(wide, 60)[0] != 0
+    sscn.sparse_conv_forward(dev(S.features(40, cin, 1)), dev(S.weights(f ** dim, cin, cout, 2)), rb)
+    for ci, co in ((cin, cout), (wide, 60)):
+        st, same = noalloc(ci, co)
+        assert st == 0 and same()
