@@ -475,6 +475,21 @@ sscn_status sscn_softmax_nll(const void* logits, int64_t n, int32_t classes, ssc
 sscn_status sscn_sgd_nesterov(float* params, const float* grads, float* momentum_buf, int64_t count, float lr,
                               float momentum, float weight_decay, void* params_bf16, hipStream_t stream);
 
+/*
+ * sscn_sgd_nesterov_many -- sscn_sgd_nesterov on n_tensors parameter tensors
+ * (a host array of their pointers and counts, read before the call returns)
+ * in as few launches as hold them.  No two tensors may overlap.
+ */
+typedef struct {
+  float* params;
+  const float* grads;
+  float* momentum_buf;
+  void* params_bf16; /* nullable */
+  int64_t count;
+} sscn_sgd_tensor;
+sscn_status sscn_sgd_nesterov_many(const sscn_sgd_tensor* tensors, int32_t n_tensors, float lr, float momentum,
+                                   float weight_decay, hipStream_t stream);
+
 /* Thread-local message describing the last failure on this thread ("" if none). */
 const char* sscn_last_error(void);
 

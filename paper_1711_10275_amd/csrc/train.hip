@@ -581,15 +581,60 @@ __global__ __launch_bounds__(64) void k_loss_finalize(const double* __restrict__
 }
 
 // g' = g + wd p; buf = momentum buf + g'; p -= lr (g' + momentum buf).
+__device__ __forceinline__ float sgd_value(float p, float g, float& b, float lr, float momentum, float wd) {
+  const float gi = g + wd * p;
+  b = momentum * b + gi;
+  return p - lr * (gi + momentum * b);
+}
 __global__ void k_sgd_nesterov(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ buf,
                                int64_t count, float lr, float momentum, float wd, uint16_t* __restrict__ p_bf16) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i] + wd * p[i];
-    const float b = momentum * buf[i] + gi;
+    float b = buf[i];
+    const float np = sgd_value(p[i], g[i], b, lr, momentum, wd);
     buf[i] = b;
-    const float np = p[i] - lr * (gi + momentum * b);
     p[i] = np;
     if (p_bf16) p_bf16[i] = f32_bf16_bits(np);
+  }
+}
+// Up to kSgdTensors tensors in one launch, their table in the kernel's
+// arguments (2.8 KB of the 4 that those may have): workgroup b takes 1024
+// elements of the tensor whose range of workgroups, [first[k], first[k + 1]),
+// holds b.  A network's parameters are many small tensors (46 of them, 8 to
+// 7k elements, in a three-level network of 8 channels), whose update is all
+// launches, not bytes.
+constexpr int kSgdTensors = 64, kSgdPer = 1024;
+struct SgdTable {
+  sscn_sgd_tensor t[kSgdTensors];
+  uint32_t first[kSgdTensors + 1];
+  int n;
+};
+__global__ __launch_bounds__(256) void k_sgd_nesterov_many(SgdTable tab, float lr, float momentum, float wd) {
+  int lo = 0, hi = tab.n;  // first[lo] <= b < first[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2;
+    if (tab.first[mid] <= blockIdx.x) lo = mid;
+    else hi = mid;
+  }
+  const sscn_sgd_tensor t = tab.t[lo];
+  const int64_t i0 = (int64_t)(blockIdx.x - tab.first[lo]) * kSgdPer + threadIdx.x;
+  constexpr int U = kSgdPer / 256;
+  float p[U], g[U], b[U];
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const int64_t i = i0 + q * 256;
+    const bool ok = i < t.count;
+    p[q] = ok ? t.params[i] : 0.f;
+    g[q] = ok ? t.grads[i] : 0.f;
+    b[q] = ok ? t.momentum_buf[i] : 0.f;
+  }
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const int64_t i = i0 + q * 256;
+    if (i >= t.count) break;
+    const float np = sgd_value(p[q], g[q], b[q], lr, momentum, wd);
+    t.momentum_buf[i] = b[q];
+    t.params[i] = np;
+    if (t.params_bf16) ((uint16_t*)t.params_bf16)[i] = f32_bf16_bits(np);
   }
 }
 
@@ -826,4 +871,39 @@ extern "C" sscn_status sscn_sgd_nesterov(float* params, const float* grads, floa
                                                      (uint16_t*)params_bf16);
   SSCN_HIP(hipGetLastError());
   return SSCN_OK;
+}
+
+extern "C" sscn_status sscn_sgd_nesterov_many(const sscn_sgd_tensor* tensors, int32_t n_tensors, float lr,
+                                              float momentum, float weight_decay, hipStream_t stream) {
+  if (n_tensors < 0 || (n_tensors > 0 && !tensors)) return fail(SSCN_ERR_INVALID_ARG, "NULL tensors or n_tensors < 0");
+  for (int32_t k = 0; k < n_tensors; ++k) {
+    const sscn_sgd_tensor& t = tensors[k];
+    if (t.count < 0) return fail(SSCN_ERR_INVALID_ARG, "count must be >= 0");
+    if (t.count > 0 && (!t.params || !t.grads || !t.momentum_buf))
+      return fail(SSCN_ERR_INVALID_ARG, "NULL params, grads or momentum buffer");
+  }
+  SgdTable tab;
+  tab.n = 0;
+  tab.first[0] = 0;
+  const auto flush = [&]() -> sscn_status {
+    if (tab.n == 0) return SSCN_OK;
+    k_sgd_nesterov_many<<<tab.first[tab.n], 256, 0, stream>>>(tab, lr, momentum, weight_decay);
+    SSCN_HIP(hipGetLastError());
+    tab.n = 0;
+    return SSCN_OK;
+  };
+  for (int32_t k = 0; k < n_tensors; ++k) {
+    const sscn_sgd_tensor& t = tensors[k];
+    if (t.count == 0) continue;
+    const int64_t groups = ceil_div(t.count, (int64_t)kSgdPer);
+    if (groups > (1 << 20)) {  // 1G elements: a launch of its own, over a bounded grid
+      SSCN_TRY(sscn_sgd_nesterov(t.params, t.grads, t.momentum_buf, t.count, lr, momentum, weight_decay, t.params_bf16,
+                                 stream));
+      continue;
+    }
+    tab.t[tab.n] = t;
+    tab.first[tab.n + 1] = tab.first[tab.n] + (uint32_t)groups;
+    if (++tab.n == kSgdTensors) SSCN_TRY(flush());
+  }
+  return flush();
 }

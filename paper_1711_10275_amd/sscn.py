@@ -44,6 +44,12 @@ class ConvOutput(ctypes.Structure):
                 ("shift", ctypes.c_void_p)]
 
 
+class SgdTensor(ctypes.Structure):
+    """sscn_sgd_tensor: one parameter tensor of sscn_sgd_nesterov_many."""
+    _fields_ = [("params", ctypes.c_void_p), ("grads", ctypes.c_void_p), ("momentum_buf", ctypes.c_void_p),
+                ("params_bf16", ctypes.c_void_p), ("count", ctypes.c_int64)]
+
+
 _lib = None
 # filter_size is at most 8, so a rule book has at most 8^3 offsets
 _MAX_OFFSETS = 512
@@ -79,6 +85,7 @@ _SIGS = {
     "sscn_add": [_vp, _i64, _vp, _i64, _i64, _i32, ctypes.c_int, _vp, _i64, _vp],
     "sscn_softmax_nll": [_vp, _i64, _i32, ctypes.c_int, _vp, _vp, _vp, _vp],
     "sscn_sgd_nesterov": [_vp, _vp, _vp, _i64, ctypes.c_float, ctypes.c_float, ctypes.c_float, _vp, _vp],
+    "sscn_sgd_nesterov_many": [_vp, _i32, ctypes.c_float, ctypes.c_float, ctypes.c_float, _vp],
     "sscn_time_next_launch": [_vp, _vp],
     "sscn_release_cached": [],
     "sscn_set_device_memory_cap": [ctypes.c_uint64],
@@ -603,21 +610,45 @@ def softmax_nll(logits, labels):
     return loss, d
 
 
-def sgd_nesterov_(params, grads, buf, lr, momentum=0.9, weight_decay=1e-4, params_bf16=None):
-    """In-place Nesterov SGD step on fp32 `params` (contiguous); refreshes
-    the bfloat16 copy if given."""
-    params = _dev_tensor(params, "params", torch.float32)
-    grads = _dev_tensor(grads, "grads", torch.float32)
-    buf = _dev_tensor(buf, "momentum buffer", torch.float32)
+def _check_sgd(params, grads, buf, params_bf16):
+    _dev_tensor(params, "params", torch.float32)
+    _dev_tensor(grads, "grads", torch.float32)
+    _dev_tensor(buf, "momentum buffer", torch.float32)
     if grads.shape != params.shape or buf.shape != params.shape:
         raise ValueError("shapes differ")
     if params_bf16 is not None:
-        params_bf16 = _dev_tensor(params_bf16, "params_bf16", torch.bfloat16)
+        _dev_tensor(params_bf16, "params_bf16", torch.bfloat16)
         if params_bf16.shape != params.shape:
             raise ValueError("bf16 copy shape differs")
+
+
+def sgd_nesterov_(params, grads, buf, lr, momentum=0.9, weight_decay=1e-4, params_bf16=None):
+    """In-place Nesterov SGD step on fp32 `params` (contiguous); refreshes
+    the bfloat16 copy if given."""
+    _check_sgd(params, grads, buf, params_bf16)
     with torch.cuda.device(params.device):
         _check(lib().sscn_sgd_nesterov(_vp_of(params), _vp_of(grads), _vp_of(buf), params.numel(), lr, momentum,
                                        weight_decay, _vp_of(params_bf16), _stream(params)))
+
+
+def sgd_nesterov_many_(items, lr, momentum=0.9, weight_decay=1e-4):
+    """sgd_nesterov_ on every (params, grads, buf, bf16 copy or None) of
+    `items` in one call; one after another where two of them share memory's
+    start or they are not all on one device."""
+    for it in items:
+        _check_sgd(*it)
+    if not items:
+        return
+    dev = items[0][0].device
+    starts = [t.data_ptr() for p, _, b, c in items for t in (p, b, c) if t is not None and t.numel()]
+    if len(set(starts)) < len(starts) or any(t.device != dev for it in items for t in it if t is not None):
+        for p, g, b, c in items:
+            sgd_nesterov_(p, g, b, lr, momentum, weight_decay, params_bf16=c)
+        return
+    arr = (SgdTensor * len(items))(*[(p.data_ptr(), g.data_ptr(), b.data_ptr(), c.data_ptr() if c is not None else None,
+                                      p.numel()) for p, g, b, c in items])
+    with torch.cuda.device(dev):
+        _check(lib().sscn_sgd_nesterov_many(arr, len(items), lr, momentum, weight_decay, _stream(items[0][0])))
 
 
 # ------------------------------------------------------------- measurement

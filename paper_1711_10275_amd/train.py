@@ -151,8 +151,10 @@ def train_step(x, labels, geom, P, lr=0.1, momentum=0.9, weight_decay=1e-4, upda
     assert not tape
 
     if update:
+        items = []
         for name, ts in P.master.items():
             for i, (p, g, b) in enumerate(zip(ts, grads[name], P.buf[name])):
                 copy = P.compute[name] if (i == 2 and P.dtype != torch.float32) else None
-                sscn.sgd_nesterov_(p, g.reshape(p.shape), b, lr, momentum, weight_decay, params_bf16=copy)
+                items.append((p, g.reshape(p.shape), b, copy))
+        sscn.sgd_nesterov_many_(items, lr, momentum, weight_decay)
     return loss, grads

@@ -85,6 +85,34 @@ def test_softmax_nll(n, k, dtype):
     assert_close(host(d), rd, dtype, "dlogits")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,k", [(255, 64), (257, 63), (256, 2), (1025, 65), (262401, 3)])
+def test_softmax_nll_row_tiles(n, k, dtype):
+    """Tiles of 256 rows: short, whole and one row over, the widest rows (66 KB
+    of LDS) and the first beyond, and more tiles than workgroups."""
+    test_softmax_nll(n, k, dtype)
+
+
+def test_sgd_nesterov_many_equals_one_by_one():
+    """Empty and one-element tensors, edges of a workgroup's 1024 elements, more
+    tensors than a launch holds, tensors without a bf16 copy, a tensor twice."""
+    rng = np.random.default_rng(8)
+    sizes = [0, 1, 1023, 1024, 1025, 5000, 70000] + [3 + i for i in range(63)]
+    draw = lambda: [dev(rng.standard_normal(n).astype(np.float32)) for n in sizes]
+    p, g, b = draw(), draw(), draw()
+    c = [torch.zeros(n, dtype=torch.bfloat16, device="cuda:0") if i % 3 else None for i, n in enumerate(sizes)]
+    for extra in ([], [(p[4], g[4], b[4], None)]):
+        items = list(zip(p, g, b, c)) + extra
+        want = {id(t): t.clone() for it in items for t in it if t is not None}
+        for it in items:
+            q = [want.get(id(t)) for t in it]
+            sscn.sgd_nesterov_(q[0], q[1], q[2], 0.1, params_bf16=q[3])
+        sscn.sgd_nesterov_many_(items, 0.1)
+        for it in items:
+            for t in it:
+                assert t is None or torch.equal(t, want[id(t)])
+
+
 def test_sgd_nesterov_two_steps():
     rng = np.random.default_rng(6)
     p0 = rng.standard_normal(1001).astype(np.float32)
