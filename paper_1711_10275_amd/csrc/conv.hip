@@ -13,6 +13,7 @@
 // wgrad: dW^o = X[in_o]^T dY[out_o], per-offset gathered contractions with
 // fp32 MFMAs, split over pairs and reduced with fp32 atomics.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include <hip/hip_ext.h>
@@ -325,54 +326,80 @@ __global__ __launch_bounds__(256) void k_conv_narrow(const T* __restrict__ X, co
 }
 
 // SSC layers of filter size 1 (every row paired with itself: the per-site
-// linear layer at the end of a network) of at most kPointMax weights: the
-// weights in LDS, a thread sums 4 columns of a row over the kdim channels in
-// order.  Memory-bound, and of less work than a row block costs to set up:
-// 99,515 sites, fp32: 32 -> 20 channels 11 us (16 on the row-block kernel
-// with its weight copy); the gradient, 20 -> 32, 14 us (25 on the column
-// kernel).
-constexpr int kPointMax = 1024;
-template <typename T, bool TR>
+// linear layer at the end of a network) of few weights: the weights in LDS; a
+// thread keeps its 4 columns, sums them over the kdim channels in order, and
+// goes from row to row without a division, reading 16 bytes of a row at once.
+// Memory-bound, and of less work than a row block costs to set up.  32 -> 20
+// channels and its gradient, fp32: 10 and 10 us at 100k sites (12 and 26 on
+// the row-block kernel with its weight copy and the column kernel), 109 and
+// 108 us at 1.96M (138 and 180).
+constexpr int kPointMax = 1024, kPointMaxRows16 = 800;
+template <typename T, bool TR, int V>
 __global__ __launch_bounds__(256) void k_conv_point(const T* __restrict__ X, const T* __restrict__ W, int kdim,
                                                     int ncols, int64_t n, int64_t rows_per_wg, Heads<T> Y) {
   extern __shared__ float wl[];
-  const int groups = (ncols + 3) / 4;
+  const int groups = (ncols + 3) / 4;  // at most 256
   stage_weights<T, TR>(W, 1, kdim, ncols, groups, wl);
   __syncthreads();
   const bool vec = heads_vec4(Y);
+  const int per_pass = 256 / groups, r = threadIdx.x / groups, g = threadIdx.x % groups;
+  if (r >= per_pass) return;
   const int64_t lo = (int64_t)blockIdx.x * rows_per_wg, hi = min<int64_t>(n, lo + rows_per_wg);
-  for (int64_t i = lo * groups + threadIdx.x; i < hi * groups; i += 256) {
-    const int64_t row = i / groups;
-    const int g = (int)(i - row * groups);
+  const float* const wg = wl + g * 4;
+  for (int64_t row = lo + r; row < hi; row += per_pass) {
     const T* x = X + row * kdim;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int k = 0; k < kdim; ++k) {
-      const float v = Elem<T>::load(x + k);
-      const float4 w = *reinterpret_cast<const float4*>(wl + (k * groups + g) * 4);
-      acc[0] = fmaf(v, w.x, acc[0]);
-      acc[1] = fmaf(v, w.y, acc[1]);
-      acc[2] = fmaf(v, w.z, acc[2]);
-      acc[3] = fmaf(v, w.w, acc[3]);
+#pragma unroll 4
+    for (int k = 0; k < kdim; k += V) {
+      float v[V];
+      if constexpr (V == 1) {
+        v[0] = Elem<T>::load(x + k);
+      } else {
+        const uint4 q = *reinterpret_cast<const uint4*>(x + k);
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (V == 4) {
+            v[i] = __uint_as_float(w[i]);
+          } else {
+            v[2 * i] = __uint_as_float(w[i] << 16);
+            v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const float4 w = *reinterpret_cast<const float4*>(wg + (k + i) * groups * 4);
+        acc[0] = fmaf(v[i], w.x, acc[0]);
+        acc[1] = fmaf(v[i], w.y, acc[1]);
+        acc[2] = fmaf(v[i], w.z, acc[2]);
+        acc[3] = fmaf(v[i], w.w, acc[3]);
+      }
     }
     store4(Y, row, 4 * g, ncols, vec, acc);
   }
 }
 
-// Whether a launch (rows of kdim channels in, ncols out) goes to these two
-// kernels: the weights and the tile's table within 48 KB of LDS for fewer than
-// 8 input channels, at most kPointMax weights for filter size 1.
-static bool narrow_eligible(const View& v, int kdim, int ncols) {
-  const size_t lds = sizeof(float) * (size_t)v.K * kdim * ((ncols + 3) / 4 * 4) + sizeof(int32_t) * kTile * (size_t)v.K;
-  return kdim < 8 && lds <= 48 * 1024;
-}
-static bool point_eligible(const View& v, int kdim, int ncols) {
-  return v.K == 1 && v.owner->submanifold && (int64_t)kdim * ncols <= kPointMax;
-}
 template <typename T>
 static bool rows_eligible(const View& v, int kdim, int ncols);
 template <typename T>
 static bool prefer_col(const View& v, int cin, int cout);
+// Whether a launch (rows of kdim channels in, ncols out) goes to these two
+// kernels: the weights and the tile's table within 48 KB of LDS for fewer than
+// 8 input channels.  For filter size 1 at most kPointMax weights, or
+// kPointMaxRows16 in bf16 where the row-block kernel takes the layer: that one
+// is the faster at 1024 weights (32 -> 32 at 500k sites: 29 us, 33 here) and
+// the slower up to 800 (40 -> 20: 28 and 25; 16 -> 16: 24 and 13), while its
+// fp32 form is the slower or equal at 1024 too (8 -> 128: 109 and 68).
+static bool narrow_eligible(const View& v, int kdim, int ncols) {
+  const size_t lds = sizeof(float) * (size_t)v.K * kdim * ((ncols + 3) / 4 * 4) + sizeof(int32_t) * kTile * (size_t)v.K;
+  return kdim < 8 && lds <= 48 * 1024;
+}
+template <typename T>
+static bool point_eligible(const View& v, int kdim, int ncols) {
+  const int most = sizeof(T) == 2 && rows_eligible<T>(v, kdim, ncols) ? kPointMaxRows16 : kPointMax;
+  return v.K == 1 && v.owner->submanifold && (int64_t)kdim * ncols <= most;
+}
 // The table that the general kernels would use for this layer: any forward or
 // backward call leaves it behind for the no-allocation forward, whose layers
 // may be wider ones on the same rule book, and which is refused without it.
@@ -386,12 +413,17 @@ static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim,
                                 hipStream_t s) {
   const int groups = (ncols + 3) / 4;
   size_t lds = sizeof(float) * (size_t)v.K * kdim * groups * 4;
-  if (point_eligible(v, kdim, ncols)) {
+  if (point_eligible<T>(v, kdim, ncols)) {
     if (v.n_out == 0) return SSCN_OK;
     SSCN_TRY(ensure_general_table<T>(v, kdim, ncols, s));
-    // about four workgroups per CU, at least one pass of 256 threads each
-    const int64_t rows = std::max<int64_t>(ceil_div(256, groups), ceil_div(v.n_out, 1024));
-    k_conv_point<T, TR><<<(unsigned)ceil_div(v.n_out, rows), 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
+    // about eight workgroups per CU, each of whole passes over 256 / groups rows
+    const int64_t per_pass = 256 / groups;
+    const int64_t rows = ceil_div(ceil_div(v.n_out, (int64_t)2048), per_pass) * per_pass;
+    // rows of whole aligned 16-byte pieces are read as such
+    constexpr int V = 16 / (int)sizeof(T);
+    const bool pieces = kdim % V == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+    const auto kern = pieces ? k_conv_point<T, TR, V> : k_conv_point<T, TR, 1>;
+    kern<<<(unsigned)ceil_div(v.n_out, rows), 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
     SSCN_HIP(hipGetLastError());
     return SSCN_OK;
   }
@@ -2369,10 +2401,15 @@ static sscn_status launch_wgrad_reg(bool zeroed, const T* X, const T* dY, const 
     const int64_t target = std::max<int64_t>(1, (int64_t)cus * per_cu / (nzc * nzo));
     // at most target / S tile ranges, so that the items fit one round
     // (a few items left for a second round would double the kernel's time)
-    // every item adds its block to the same dW elements of its offset with
+    // Every item adds its block to the dW elements of its offset with
     // atomics, which take turns: with few offsets (filter size 1 above all)
-    // at most 256 ranges (32 -> 20 channels at 99,515 sites: 38 -> 22 us)
-    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>(target / S, 256));
+    // the time is ranges x one turn + tiles / ranges x one tile, least at
+    // ranges ~ sqrt(tiles); up to one item per CU they hardly meet, so 256
+    // until twice as many pay.  All ranges that fit / 256 / this: 32 -> 20
+    // channels, fp32, 99,515 sites 41 / 21 / 21 us; 16 -> 16, bf16, 1.96M
+    // sites 79 / 168 / 72 us.
+    const int64_t root = (int64_t)(8.0 * std::sqrt((double)v.st->n_tiles));
+    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>(target / S, root < 512 ? 256 : root));
     const int64_t tr2 = std::max<int64_t>(1, ceil_div(v.st->n_tiles, ranges));
     const int64_t total = ceil_div(v.st->n_tiles, tr2) * S;
     // deterministic mode: every item block to its own slot, then a
@@ -2741,7 +2778,7 @@ static sscn_status check_conv_args(sscn_rulebook rb, int32_t c_in, int32_t c_out
 // column's reduction channels.
 template <typename T>
 static sscn_status forward_t(const T* X, const T* W, const View& v, int cin, int cout, const Heads<T>& Y, hipStream_t s) {
-  if (narrow_eligible(v, cin, cout) || point_eligible(v, cin, cout)) return launch_small<T, true>(X, W, v, cin, cout, Y, s);
+  if (narrow_eligible(v, cin, cout) || point_eligible<T>(v, cin, cout)) return launch_small<T, true>(X, W, v, cin, cout, Y, s);
   if (rows_eligible<T>(v, cin, cout)) {
     if (v.n_out == 0) return SSCN_OK;
     if constexpr (sizeof(T) == 4) {
@@ -2893,7 +2930,7 @@ extern "C" sscn_status sparse_conv_backward(const void* features, const void* we
     const View vt = transposed_view(rb);
     if (dtype == SSCN_F32) {
       Heads<float> h = plain_heads((float*)dgrad, c_in);
-      if (narrow_eligible(vt, c_out, c_in) || point_eligible(vt, c_out, c_in)) {
+      if (narrow_eligible(vt, c_out, c_in) || point_eligible<float>(vt, c_out, c_in)) {
         st = launch_small<float, false>((const float*)dout, (const float*)weights, vt, c_out, c_in, h, stream);
       } else if (rows_eligible<float>(vt, c_out, c_in)) {
         if (wgrad) { h.zero = wgrad; h.n_zero = w_total; w_zeroed = true; }
@@ -2915,7 +2952,7 @@ extern "C" sscn_status sparse_conv_backward(const void* features, const void* we
       }
     } else {
       Heads<bf16_t> h = plain_heads((bf16_t*)dgrad, c_in);
-      if (narrow_eligible(vt, c_out, c_in) || point_eligible(vt, c_out, c_in)) {
+      if (narrow_eligible(vt, c_out, c_in) || point_eligible<bf16_t>(vt, c_out, c_in)) {
         st = launch_small<bf16_t, false>((const bf16_t*)dout, (const bf16_t*)weights, vt, c_out, c_in, h, stream);
       } else if (rows_eligible<bf16_t>(vt, c_out, c_in)) {
         if (wgrad) { h.zero = wgrad; h.n_zero = w_total; w_zeroed = true; }
