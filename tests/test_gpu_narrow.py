@@ -55,6 +55,30 @@ def test_forward_dgrad(kind, f, s, cin, cout, dtype):
     assert_close(host(dw), rdw, "f32", "wgrad")
 
 
+@pytest.mark.parametrize("cin,cout", [(8, 6), (8, 20), (16, 6), (16, 20), (32, 6), (32, 20), (32, 32), (40, 13), (24, 40),
+                                      (20, 12), (36, 8), (13, 33), (50, 20), (64, 16), (4, 5)])
+def test_per_site_bits_fp32(cin, cout):
+    """A per-site layer in fp32 gives the bits of the kernels that it runs on
+    otherwise: an SSC(3) layer of isolated sites, whose centre offset alone has
+    pairs, over the same rows."""
+    g = np.arange(0, 64, 3)
+    c = np.stack(np.meshgrid(g, g, g[:5], indexing="ij"), -1).reshape(-1, 3)
+    c = dev(np.concatenate([np.zeros((c.shape[0], 1)), c], 1).astype(np.int32))
+    one, three = (sscn.ssc_rulebook_build(c, (64, 64, 64), f) for f in (1, 3))
+    n = one.n_in
+    assert three.n_pairs == n
+    X, W, G = dev(S.features(n, cin, 1)), dev(S.weights(1, cin, cout, 2)), dev(S.features(n, cout, 3))
+    W3 = torch.zeros(27, cin, cout, device="cuda")
+    W3[13] = W[0]
+    assert torch.equal(sscn.sparse_conv_forward(X, W, one), sscn.sparse_conv_forward(X, W3, three))
+    if cin % 8 or cin in (8, 24):  # the per-site kernel: rows that are not 16-byte aligned add up in the same order
+        odd = torch.zeros(n * cin + 1, device="cuda")[1:].view(n, cin)
+        odd.copy_(X)
+        assert torch.equal(sscn.sparse_conv_forward(odd, W, one), sscn.sparse_conv_forward(X, W, one))
+    dx = [sscn.sparse_conv_backward(X, w, G, rb, wgrad=False)[0] for w, rb in ((W, one), (W3, three))]
+    assert torch.equal(*dx)
+
+
 @pytest.mark.parametrize("dim,f,cin,cout", [(4, 1, 32, 20), (3, 3, 4, 16), (4, 1, 20, 32)])
 def test_tables_for_the_no_allocation_forward(dim, f, cin, cout):
     """One ordinary call leaves the tables that a wider layer of the same kind
