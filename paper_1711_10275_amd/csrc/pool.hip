@@ -12,7 +12,8 @@
 //   upsample        sum over the transposed direction (one pair per row, f = s)
 //   its backward    sum over the SC direction
 //
-// One output-stationary kernel covers all of them: a workgroup owns 64
+// Two output-stationary kernels cover all of them (k_pool_walk for what has
+// many offsets and few pairs).  The main one, k_pool: a workgroup owns 64
 // output rows (one tile of the direction's storage) and a run of channels.
 // It first writes the tile's pairs into an LDS table (input row by offset and
 // output row, -1 for none; within one offset every output row has at most one
@@ -27,12 +28,14 @@
 // each and 4 bytes a lane, were bound by that walk's latency: 231 us.)
 #include "internal.h"
 #include "numeric.h"
+#include "routes.h"
 
 namespace sscn {
 
 namespace {
 
 enum PoolMode { kSum = 0, kMax = 1, kMaxBack = 2 };
+constexpr int kPoolCols = 64;
 constexpr uint8_t kNoArg = 255;  // the zero vector is the maximum
 
 // V consecutive values of a row, or of its winning offsets.
@@ -190,6 +193,61 @@ __global__ __launch_bounds__(256) void k_pool(const T* __restrict__ X, const uin
   }
 }
 
+// The same results, bit for bit, by a walk over the pairs: the tile's rows and
+// 64 channels of them in LDS, the offsets in order, the four wavefronts taking
+// an offset's pairs in turn (a row has one at most), a barrier after each
+// offset.  For many offsets with a pair at few of them, and for long rows of
+// single channels: its time goes with the offsets of a tile and the pairs, not
+// with the offsets of every row (pool_takes_table).
+template <typename T, int MODE>
+__global__ __launch_bounds__(256) void k_pool_walk(const T* __restrict__ X, const uint8_t* __restrict__ arg_in,
+                                                   const int64_t* __restrict__ seg, int64_t n_tiles,
+                                                   const int32_t* __restrict__ in_rows,
+                                                   const int32_t* __restrict__ out_rows, int K, int mirror,
+                                                   int64_t n_out, int c, float scale, T* __restrict__ Y,
+                                                   uint8_t* __restrict__ arg_out) {
+  __shared__ float acc[kPlanRows][kPoolCols];
+  __shared__ uint8_t arg[kPlanRows][kPoolCols];
+  const int64_t t = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = blockIdx.y * kPoolCols + lane;
+  const bool live = col < c;
+  const int64_t row0 = t * kPlanRows;
+  for (int r = wave; r < kPlanRows; r += 4) {
+    acc[r][lane] = 0.f;
+    arg[r][lane] = kNoArg;
+  }
+  __syncthreads();
+  for (int o = 0; o < K; ++o) {
+    const int so = mirror ? K - 1 - o : o;
+    const int64_t p0 = seg[(int64_t)so * n_tiles + t], p1 = seg[(int64_t)so * n_tiles + t + 1];
+    for (int64_t p = p0 + wave; p < p1; p += 4) {
+      const int64_t j = in_rows[p];
+      const int r = (int)(out_rows[p] - row0);
+      if (!live) continue;
+      const float v = ld(X + j * c + col);
+      if constexpr (MODE == kSum) {
+        acc[r][lane] += v;
+      } else if constexpr (MODE == kMax) {
+        if (v > acc[r][lane]) {
+          acc[r][lane] = v;
+          arg[r][lane] = (uint8_t)o;
+        }
+      } else {
+        if (arg_in[j * c + col] == (uint8_t)o) acc[r][lane] += v;
+      }
+    }
+    __syncthreads();
+  }
+  if (!live) return;
+  for (int r = wave; r < kPlanRows; r += 4) {
+    const int64_t row = row0 + r;
+    if (row >= n_out) break;
+    st(Y + row * c + col, MODE == kSum ? acc[r][lane] * scale : acc[r][lane]);
+    if constexpr (MODE == kMax) arg_out[row * c + col] = arg[r][lane];
+  }
+}
+
 template <typename T, int MODE>
 sscn_status launch_pool(const View& v, const void* X, const uint8_t* arg_in, int c, float scale, void* Y,
                         uint8_t* arg_out, hipStream_t s) {
@@ -206,6 +264,13 @@ sscn_status launch_pool(const View& v, const void* X, const uint8_t* arg_in, int
   // fewer where the rows are shorter
   int pb = vec ? 3 : 6;
   while (pb > 0 && (1 << (pb - 1)) >= pieces) --pb;
+  if (!pool_takes_table(v.K, v.n_pairs, v.n_out, tiles, pieces, pb)) {
+    const dim3 grid((unsigned)tiles, (unsigned)ceil_div(c, kPoolCols));
+    k_pool_walk<T, MODE><<<grid, 256, 0, s>>>((const T*)X, arg_in, v.st->seg, tiles, v.st->in_rows, v.st->out_rows,
+                                              v.K, v.mirror ? 1 : 0, v.n_out, c, scale, (T*)Y, arg_out);
+    SSCN_HIP(hipGetLastError());
+    return SSCN_OK;
+  }
   const dim3 grid((unsigned)tiles, (unsigned)ceil_div(pieces, 1 << pb));
   const size_t lds = sizeof(int32_t) * kPlanRows * (size_t)v.K;
   auto kern = vec ? k_pool<T, MODE, V> : k_pool<T, MODE, 1>;

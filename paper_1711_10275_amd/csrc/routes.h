@@ -1,0 +1,48 @@
+// Which of two kernels takes a call: rules on sizes and numbers of pairs alone
+// (host code without HIP, so that a test can hold them against measured times).
+#pragma once
+
+#include <cstdint>
+
+namespace sscn {
+
+// Pooling: the table kernel (k_pool) or the walk over the pairs (k_pool_walk).
+// pieces: pieces of a row (16 bytes, or one channel); 2^pb of them per
+// workgroup, so that a thread takes 2^pb / 4 of the tile's 64 rows.
+//
+// The table kernel's threads look up all K offsets of each of their rows,
+// whether the row has a pair there or not, and every column group of a tile
+// writes the table again.  The walk takes K steps with a barrier after each, of
+// one pair per wavefront at a time.  So the table wins while a row has a pair
+// at a good part of the offsets and a thread has few rows; the measure is its
+// lookups per pair and thread, with the lanes that have no piece counted in;
+// many tiles hide more of them.
+// Measured us, table against walk (voxelised surfaces):
+//   K  pairs/row  channels          table   walk   lookups
+//   8     3.9     64 fp32, 100k       9.9   38.2       4    average
+//   27    1       16 fp32, 100k      10.6   18.6      27    its gradient
+//   27    1       36 fp32, 100k      24.1   19.1      96
+//   64    1       64 fp32, 1M         297    264     128
+//   64    1       13 fp32, 2k        23.8   18.9     315
+//   125   1       64 fp32, 100k      98.2   59.1     250
+//   64    1        5 fp32, 1M         136    253     205
+//   216   1       64 fp32, 100k       359   92.2     432
+//   512   1       64 fp32, 100k      1528    196    1024
+//   512   61      64 fp32, 100k       177    647      17    average
+// Threads of 8 rows and more (single channels of rows of 17 and more) lose to
+// the walk where few tiles leave their chain of rows bare (27 offsets, 100 bf16
+// channels, 2k sites: average 48.6 against 31.4); beyond 512 workgroups and at a
+// pair per 5 offsets the chip is full and they win (33 fp32 channels, 500k:
+// 61 against 129).
+inline bool pool_takes_table(int K, int64_t n_pairs, int64_t n_out, int64_t tiles, int pieces, int pb) {
+  const int64_t groups = (pieces + (1 << pb) - 1) >> pb;
+  const double pairs = n_out > 0 ? (double)n_pairs / (double)n_out : 0.0;  // of a row
+  if (K <= 5 * pairs && tiles * groups >= 512) return true;
+  if (pb > (K <= 27 ? 5 : 4)) return false;
+  const double rows = pb > 2 ? (double)(1 << pb) / 4 : 1.0, idle = (double)(groups << pb) / pieces;
+  const double lookups = K * rows * idle;
+  const int most = groups > 1 || K > 128 ? 64 : K <= 64 && pb <= 4 && tiles >= 2048 ? 270 : 90;
+  return lookups <= most * pairs;
+}
+
+}  // namespace sscn

@@ -122,3 +122,24 @@ def test_average_pool_512_offsets(dtype):
     odd.copy_(dev(X, TD[dtype]))
     assert odd.data_ptr() % 16
     assert_close(host(sscn.pool_forward(odd, rb, "avg")[0]), O.avg_pool(X, orb), dtype, "AP unaligned")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("size,f,s,ch", [((16, 16, 16), 4, 4, 13), ((15, 15, 15), 5, 5, 64), ((16, 16, 16), 4, 4, 130),
+                                         ((17, 17, 17), 3, 2, 33), ((15, 15, 15), 3, 3, 36), ((18, 18, 18), 6, 6, 1)])
+def test_pool_walk_paths(size, f, s, ch, dtype):
+    """Both sides of the choice between the table and the walk over the pairs:
+    a forward on one and its gradient on the other, long rows of single
+    channels, two and three column groups with a short last one."""
+    c = small_set(360 + ch, size, batch=2, density=0.2)
+    _check_pool(c, size, f, s, ch, dtype, 370 + ch)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_average_pool_512_offsets_gradient(dtype):
+    """The largest filter, one pair a row: the walk."""
+    size = (16, 16, 16)
+    c = small_set(351, size, batch=2, density=0.2)
+    rb, orb = sscn.sc_rulebook_build(dev(c), size, 8, 8), O.sc_rulebook(c, size, 8, 8)
+    G = _feat(rb.n_out, 20, 352, dtype)
+    assert_close(host(sscn.pool_backward(dev(G, TD[dtype]), rb, "avg")), O.avg_pool_backward(G, orb), dtype, "AP 8^3")

@@ -1,0 +1,83 @@
+"""The rules that choose between two kernels, held against measured times: each
+takes the kernel that was the faster, over the range and not at single shapes.
+The rules are host code without HIP and are compiled here by themselves."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1711_10275_amd", "csrc")
+
+WRAP = """
+#include "routes.h"
+extern "C" int pool_table(int K, long long n_pairs, long long n_out, int pieces, int pb) {
+  return sscn::pool_takes_table(K, n_pairs, n_out, (n_out + 63) / 64, pieces, pb);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("routes")
+    (d / "wrap.cpp").write_text(WRAP)
+    so = str(d / "wrap.so")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "wrap.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.pool_table.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    return lib
+
+
+def _pieces(channels, dtype):
+    """(pieces, pb) of a row as launch_pool forms them, of aligned tensors."""
+    v = 4 if dtype == "f32" else 8
+    pieces, pb = (channels // v, 3) if channels % v == 0 else (channels, 6)
+    while pb and 1 << (pb - 1) >= pieces:
+        pb -= 1
+    return pieces, pb
+
+
+# filter, rows written, pairs, channels, dtype, us of the table kernel, us of the walk
+POOL = [
+    (2, 25821, 100000, 64, "f32", 9.8, 38.2),  # average
+    (2, 100000, 100000, 64, "f32", 12.7, 18.2),  # its gradient
+    (3, 11547, 100000, 64, "f32", 14.5, 59.6),  # average
+    (3, 100000, 100000, 16, "f32", 10.6, 18.6),  # its gradient
+    (3, 100000, 100000, 36, "f32", 24.1, 19.1),  # its gradient
+    (3, 32426, 275876, 32, "bf16", 10.5, 43.9),  # average
+    (4, 71432, 1000000, 64, "f32", 72.1, 303.1),  # average
+    (4, 1000000, 1000000, 64, "f32", 296.7, 264.1),  # its gradient
+    (4, 1000000, 1000000, 5, "f32", 135.9, 252.5),  # its gradient
+    (3, 500000, 500000, 13, "f32", 59.7, 86.3),  # its gradient
+    (4, 2000, 2000, 13, "f32", 23.8, 18.9),  # its gradient
+    (4, 100000, 792014, 32, "f32", 30.7, 96.8),  # its gradient
+    (5, 100000, 100000, 64, "f32", 98.2, 59.1),  # its gradient
+    (5, 20000, 20000, 100, "f32", 43.0, 33.9),  # its gradient
+    (6, 100000, 100000, 16, "f32", 118.6, 79.4),  # its gradient
+    (6, 100000, 100000, 64, "f32", 340.3, 96.5),  # its gradient
+    (6, 1000000, 1000000, 1, "f32", 893.7, 662.0),  # its gradient
+    (8, 100000, 100000, 64, "f32", 1527.9, 195.7),  # its gradient
+    (8, 100000, 100000, 100, "bf16", 7926.7, 360.3),  # its gradient
+    (8, 1642, 100000, 64, "f32", 177.1, 646.5),  # average
+    (2, 620, 2000, 100, "bf16", 19.8, 17.0),  # average
+    (2, 2000, 2000, 100, "bf16", 15.6, 10.2),  # its gradient
+    (3, 310, 2000, 100, "bf16", 54.7, 34.7),  # maximum
+    (3, 9511, 67396, 33, "f32", 41.2, 34.6),  # average
+    (3, 62481, 500000, 33, "f32", 61.1, 129.2),  # average
+    (2, 100000, 100000, 33, "bf16", 21.1, 13.7),  # its gradient
+    (8, 52, 2000, 13, "bf16", 201.9, 169.1),  # average
+    (2, 136670, 500000, 20, "bf16", 30.3, 54.9),  # average
+    (2, 274166, 1000000, 13, "bf16", 31.5, 104.8),  # maximum
+]
+
+
+def test_pool_rule_takes_the_faster_kernel(rules):
+    for f, n_out, n_pairs, c, dtype, table, walk in POOL:
+        got = bool(rules.pool_table(f ** 3, n_pairs, n_out, *_pieces(c, dtype)))
+        assert got == (table < walk), (f, n_out, n_pairs, c, dtype)
+
+
+def test_pool_rule_at_its_ends(rules):
+    assert not rules.pool_table(8, 0, 100, *_pieces(64, "f32"))  # no pairs: nothing to look up
+    assert not rules.pool_table(8, 0, 0, *_pieces(1, "f32"))
+    assert rules.pool_table(1, 100, 100, *_pieces(1, "bf16"))
