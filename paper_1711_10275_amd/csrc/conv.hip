@@ -15,10 +15,12 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
 #include "internal.h"
+#include "routes.h"
 
 namespace sscn {
 
@@ -330,15 +332,16 @@ __global__ __launch_bounds__(256) void k_conv_narrow(const T* __restrict__ X, co
 // thread keeps its 4 columns, sums them over the kdim channels, and goes from
 // row to row without a division, reading 16 bytes of a row at once.
 // Memory-bound, and of less work than a row block costs to set up.  20 -> 32
-// channels and its gradient's 32 -> 20 in fp32, 100k sites: 10 us (26 on the
+// channels in fp32: 10 us at 100k sites and 109 at 1.96M (28 and 185 on the
 // column kernel).
 //
 // fp32 sums take the channels in the order of the kernel that runs the layer
 // otherwise, so that a result does not depend on the choice: MFMAs of four
 // channels, a channel from each quarter of a window of WIN channels, one
-// multiply-add after another (WIN: 32 in the row-block kernel, 16 in the column
-// kernel, 64 in the generic one).  WIN = 0 (bf16): in ascending order.
-constexpr int kPointMax = 1024, kPointMaxRows16 = 800;
+// multiply-add after another (WIN: 16 in the column kernel, 64 in the generic
+// one, 32 in the row-block kernel).  WIN = 0: in ascending order (bf16, and rows
+// within the first quarter, where that is the same: of the row-block kernel's
+// layers only rows of 8 channels come here).
 template <typename T, bool TR, int V, int WIN>
 __global__ __launch_bounds__(256) void k_conv_point(const T* __restrict__ X, const T* __restrict__ W, int kdim,
                                                     int ncols, int64_t n, int64_t rows_per_wg, Heads<T> Y) {
@@ -354,7 +357,7 @@ __global__ __launch_bounds__(256) void k_conv_point(const T* __restrict__ X, con
   for (int64_t row = lo + r; row < hi; row += per_pass) {
     const T* x = X + row * kdim;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    const auto add = [&](float v, int k) {
+    const auto add = [&](float v, int k) __attribute__((always_inline)) {
       const float4 w = *reinterpret_cast<const float4*>(wg + k * groups * 4);
       acc[0] = fmaf(v, w.x, acc[0]);
       acc[1] = fmaf(v, w.y, acc[1]);
@@ -362,43 +365,74 @@ __global__ __launch_bounds__(256) void k_conv_point(const T* __restrict__ X, con
       acc[3] = fmaf(v, w.w, acc[3]);
     };
     if constexpr (WIN > 0) {
-      static_assert(sizeof(T) == 4 && (V == 1 || V == 4), "fp32");
+      static_assert(sizeof(T) == 4 && (V == 1 || WIN == 16), "fp32");
       constexpr int Q = WIN / 4;  // channels of a quarter
-      for (int k0 = 0; k0 < kdim; k0 += WIN) {
-#pragma unroll 4
-        for (int e0 = 0; e0 < Q; e0 += V) {
-          float v[4][V];
+      // channels e0 .. e1 - 1 of the first M quarters of the window at k0; the
+      // fences keep the compiler from reading all their weights ahead (160
+      // VGPRs, three wavefronts a SIMD)
+      const auto part = [&](auto m, int k0, int e0, int e1) __attribute__((always_inline)) {
+        constexpr int M = decltype(m)::value;
+        constexpr int S = WIN == 16 ? 4 : 2;  // of each at once (whole fours in the column kernel's rows)
+        int e = e0;
+#pragma unroll 1
+        for (; e + S <= e1; e += S) {
+          float v[M][S];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int k = k0 + Q * q + e0;
-            if (k >= kdim) continue;  // V divides kdim
+          for (int q = 0; q < M; ++q) {
+            const T* src = x + k0 + Q * q + e;
             if constexpr (V == 4) {
-              const float4 p = *reinterpret_cast<const float4*>(x + k);
+              const float4 p = *reinterpret_cast<const float4*>(src);
               v[q][0] = p.x; v[q][1] = p.y; v[q][2] = p.z; v[q][3] = p.w;
             } else {
-              v[q][0] = Elem<T>::load(x + k);
+#pragma unroll
+              for (int i = 0; i < S; ++i) v[q][i] = Elem<T>::load(src + i);
             }
           }
 #pragma unroll
-          for (int e = 0; e < V; ++e)
+          for (int i = 0; i < S; ++i) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (k0 + Q * q + e0 < kdim) add(v[q][e], k0 + Q * q + e0 + e);
+            for (int q = 0; q < M; ++q) add(v[q][i], k0 + Q * q + e + i);
+            asm volatile("" ::: "memory");
+          }
         }
-      }
+        if constexpr (S == 2) {
+          if (e < e1) {
+            float v[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q) v[q] = Elem<T>::load(x + k0 + Q * q + e);
+#pragma unroll
+            for (int q = 0; q < M; ++q) add(v[q], k0 + Q * q + e);
+          }
+        }
+      };
+      const auto quarters = [&](int m, int k0, int e0, int e1) __attribute__((always_inline)) {
+        if (m == 1) part(std::integral_constant<int, 1>{}, k0, e0, e1);
+        else if (m == 2) part(std::integral_constant<int, 2>{}, k0, e0, e1);
+        else if (m == 3) part(std::integral_constant<int, 3>{}, k0, e0, e1);
+        else if (m == 4) part(std::integral_constant<int, 4>{}, k0, e0, e1);
+      };
+      int k0 = 0;
+      for (; k0 + WIN <= kdim; k0 += WIN) part(std::integral_constant<int, 4>{}, k0, 0, Q);
+      // the last window: whole quarters, and the first channels of one more
+      const int whole = (kdim - k0) / Q, rest = (kdim - k0) % Q;
+      quarters(whole + 1, k0, 0, rest);
+      quarters(whole, k0, rest, Q);
     } else {
 #pragma unroll 4
       for (int k = 0; k < kdim; k += V) {
         if constexpr (V == 1) {
           add(Elem<T>::load(x + k), k);
         } else {
-          static_assert(sizeof(T) == 2 && V == 8, "bf16");
           const uint4 q = *reinterpret_cast<const uint4*>(x + k);
           const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            add(__uint_as_float(w[i] << 16), k + 2 * i);
-            add(__uint_as_float(w[i] & 0xffff0000u), k + 2 * i + 1);
+            if constexpr (V == 4) {
+              add(__uint_as_float(w[i]), k + i);
+            } else {
+              add(__uint_as_float(w[i] << 16), k + 2 * i);
+              add(__uint_as_float(w[i] & 0xffff0000u), k + 2 * i + 1);
+            }
           }
         }
       }
@@ -411,16 +445,9 @@ template <typename T>
 static bool rows_eligible(const View& v, int kdim, int ncols);
 template <typename T>
 static bool prefer_col(const View& v, int cin, int cout);
-static bool rows_split(const View& v, int kdim, int ncols);
 // Whether a launch (rows of kdim channels in, ncols out) goes to these two
 // kernels: the weights and the tile's table within 48 KB of LDS for fewer than
-// 8 input channels.  For filter size 1 at most kPointMax weights, or
-// kPointMaxRows16 in bf16 where the row-block kernel takes the layer: that one
-// is the faster at 1024 weights (32 -> 32 at 500k sites: 29 us, 33 here) and
-// the slower up to 800 (40 -> 20: 28 and 25; 16 -> 16: 24 and 13).  fp32 rows
-// that the row-block kernel takes as bf16 parts stay there: a multiply-add
-// chain rounds differently (1e-7 of the sum), which a network's later steps
-// amplify where a sum close to zero changes its sign.
+// 8 input channels; for filter size 1 where point_is_faster says so.
 static bool narrow_eligible(const View& v, int kdim, int ncols) {
   const size_t lds = sizeof(float) * (size_t)v.K * kdim * ((ncols + 3) / 4 * 4) + sizeof(int32_t) * kTile * (size_t)v.K;
   return kdim < 8 && lds <= 48 * 1024;
@@ -429,8 +456,8 @@ template <typename T>
 static bool point_eligible(const View& v, int kdim, int ncols) {
   if (v.K != 1 || !v.owner->submanifold) return false;
   const bool rows = rows_eligible<T>(v, kdim, ncols);
-  if (sizeof(T) == 4 && kdim % 8 == 0 && (!rows || rows_split(v, kdim, ncols))) return false;
-  return (int64_t)kdim * ncols <= (sizeof(T) == 2 && rows ? kPointMaxRows16 : kPointMax);
+  if (sizeof(T) == 4 && kdim % 8 == 0 && !rows) return false;  // more than 2^32 bytes: as the general kernels have it
+  return point_is_faster(sizeof(T), rows, kdim, ncols);
 }
 // The table that the general kernels would use for this layer: any forward or
 // backward call leaves it behind for the no-allocation forward, whose layers
@@ -456,12 +483,11 @@ static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim,
     const bool pieces = kdim % V == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
     const auto kern = [&] {
       if constexpr (sizeof(T) == 4) {
-        if (rows_eligible<T>(v, kdim, ncols)) return pieces ? k_conv_point<T, TR, V, 32> : k_conv_point<T, TR, 1, 32>;
-        if (prefer_col<T>(v, kdim, ncols)) return pieces ? k_conv_point<T, TR, V, 16> : k_conv_point<T, TR, 1, 16>;
-        return pieces ? k_conv_point<T, TR, V, 64> : k_conv_point<T, TR, 1, 64>;
-      } else {
-        return pieces ? k_conv_point<T, TR, V, 0> : k_conv_point<T, TR, 1, 0>;
+        const int win = rows_eligible<T>(v, kdim, ncols) ? 32 : prefer_col<T>(v, kdim, ncols) ? 16 : 64;
+        if (win == 16 && kdim > 4) return pieces ? k_conv_point<T, TR, V, 16> : k_conv_point<T, TR, 1, 16>;
+        if (win == 64 && kdim > 16) return k_conv_point<T, TR, 1, 64>;
       }
+      return pieces ? k_conv_point<T, TR, V, 0> : k_conv_point<T, TR, 1, 0>;
     }();
     kern<<<(unsigned)ceil_div(v.n_out, rows), 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
     SSCN_HIP(hipGetLastError());

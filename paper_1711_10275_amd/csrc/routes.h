@@ -45,4 +45,35 @@ inline bool pool_takes_table(int K, int64_t n_pairs, int64_t n_out, int64_t tile
   return lookups <= most * pairs;
 }
 
+// Per-site layers (SSC, filter size 1) of kdim channels in and ncols out: the
+// per-site kernel (k_conv_point) or what runs other layers.  rows: the row-block
+// kernel takes the layer.
+//
+// A lane walks one row, its neighbours' rows lie kdim elements apart, and each
+// row is read once per 4 columns: long rows of few columns leave the loads
+// scattered, which the general kernels' staged rows are not.  So: at most 1024
+// weights, and rows as long as these us, per-site kernel against the other, allow:
+//   fp32, 4-channel pieces  36 -> 28   500k    34   54    44 -> 4   1.96M  134  102
+//                           44 -> 20   1.96M  145  179    60 -> 16  1.96M  178  132
+//   single channels         33 -> 31   500k    60  101    50 -> 4   1.96M  402  198
+//                           50 -> 20   1.96M  363  409    70 -> 4   500k   146   84
+//                           70 -> 12   500k    63   93    33 -> 8   1.96M  175  163
+//   bf16, row-block         40 -> 20   500k    25   31    80 -> 4   500k    29   28
+//                           64 -> 12   500k    25   27    200 -> 4  500k    64   47
+// bf16 layers of the row-block kernel also count the columns that fill a group
+// of four (32 -> 25: 32 against 30 us).
+// fp32 rows that the row-block kernel takes as bf16 parts (16 channels, 32 and
+// more) stay there whatever their time: a multiply-add chain rounds differently
+// (1e-7 of the sum), and a network's later steps amplify that where a sum close
+// to zero changes its sign.  So do rows of 24 (24 -> 40: 51 us at 500k there, 75
+// here in the row-block kernel's order).
+inline bool point_is_faster(int elem_bytes, bool rows, int kdim, int ncols) {
+  const int groups = (ncols + 3) / 4;
+  if ((int64_t)kdim * ncols > 1024) return false;
+  if (elem_bytes == 2 && rows) return kdim <= 64 && (int64_t)kdim * groups * 4 <= 800;
+  if (elem_bytes == 4 && rows) return kdim == 8;
+  if (elem_bytes == 4 && kdim % 4 == 0) return kdim <= (groups >= 5 ? 44 : 40);
+  return kdim <= (groups >= 3 ? 24 : 16) * groups;
+}
+
 }  // namespace sscn

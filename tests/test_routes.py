@@ -14,6 +14,9 @@ WRAP = """
 extern "C" int pool_table(int K, long long n_pairs, long long n_out, int pieces, int pb) {
   return sscn::pool_takes_table(K, n_pairs, n_out, (n_out + 63) / 64, pieces, pb);
 }
+extern "C" int point(int elem_bytes, int kdim, int ncols) {
+  return sscn::point_is_faster(elem_bytes, kdim % 8 == 0, kdim, ncols);
+}
 """
 
 
@@ -81,3 +84,26 @@ def test_pool_rule_at_its_ends(rules):
     assert not rules.pool_table(8, 0, 100, *_pieces(64, "f32"))  # no pairs: nothing to look up
     assert not rules.pool_table(8, 0, 0, *_pieces(1, "f32"))
     assert rules.pool_table(1, 100, 100, *_pieces(1, "bf16"))
+
+
+# reduction channels, columns, dtype, us of the per-site kernel, us of the general kernels
+# (500k sites, or 1.96M where that is the closer pair)
+POINT = [
+    (36, 28, "f32", 34.2, 54.4), (36, 8, "f32", 22.3, 31.5), (20, 32, "f32", 25.1, 55.4), (12, 48, "f32", 26.6, 92.7),
+    (8, 128, "f32", 67.0, 107.1), (24, 40, "f32", 75.2, 54.8), (13, 70, "f32", 61.2, 174.3), (70, 13, "f32", 68.2, 91.8),
+    (33, 31, "f32", 60.1, 100.7), (5, 160, "f32", 95.7, 290.9), (70, 4, "f32", 145.7, 83.9), (70, 12, "f32", 63.3, 93.1), (33, 8, "f32", 174.8, 163.3),
+    (44, 4, "f32", 133.9, 102.1), (44, 20, "f32", 144.8, 178.8), (50, 4, "f32", 401.8, 198.1), (50, 20, "f32", 362.9, 409.4),
+    (60, 16, "f32", 178.0, 132.1), (100, 10, "f32", 270.7, 194.8), (100, 7, "f32", 243.1, 184.9),
+    (40, 20, "bf16", 25.2, 30.8), (32, 20, "bf16", 23.3, 32.7), (16, 16, "bf16", 14.1, 25.2), (64, 12, "bf16", 24.9, 27.0),
+    (80, 4, "bf16", 29.1, 28.1), (128, 6, "bf16", 34.2, 29.6), (200, 4, "bf16", 64.4, 46.6), (400, 2, "bf16", 118.0, 104.3),
+    (32, 25, "bf16", 32.4, 30.2), (50, 20, "bf16", 35.4, 118.1), (70, 12, "bf16", 51.8, 78.2), (70, 4, "bf16", 145.4, 71.3),
+    (100, 4, "bf16", 166.2, 95.4), (3, 64, "bf16", 28.2, 102.1),
+]
+
+
+def test_per_site_rule_takes_the_faster_kernel(rules):
+    for kdim, ncols, dtype, here, general in POINT:
+        assert bool(rules.point(4 if dtype == "f32" else 2, kdim, ncols)) == (here < general), (kdim, ncols, dtype)
+    # fp32 rows taken as bf16 parts keep their rounding
+    assert not any(rules.point(4, kdim, 4) for kdim in (16, 24, 32, 40, 64, 128))
+    assert not rules.point(4, 65536, 65536)  # the product of the largest widths stays in range
