@@ -446,11 +446,10 @@ static bool rows_eligible(const View& v, int kdim, int ncols);
 template <typename T>
 static bool prefer_col(const View& v, int cin, int cout);
 // Whether a launch (rows of kdim channels in, ncols out) goes to these two
-// kernels: the weights and the tile's table within 48 KB of LDS for fewer than
-// 8 input channels; for filter size 1 where point_is_faster says so.
+// kernels.
+template <typename T>
 static bool narrow_eligible(const View& v, int kdim, int ncols) {
-  const size_t lds = sizeof(float) * (size_t)v.K * kdim * ((ncols + 3) / 4 * 4) + sizeof(int32_t) * kTile * (size_t)v.K;
-  return kdim < 8 && lds <= 48 * 1024;
+  return narrow_is_faster(sizeof(T), v.K, kdim, ncols, v.n_pairs, v.n_out);
 }
 template <typename T>
 static bool point_eligible(const View& v, int kdim, int ncols) {
@@ -2844,7 +2843,7 @@ static sscn_status check_conv_args(sscn_rulebook rb, int32_t c_in, int32_t c_out
 // column's reduction channels.
 template <typename T>
 static sscn_status forward_t(const T* X, const T* W, const View& v, int cin, int cout, const Heads<T>& Y, hipStream_t s) {
-  if (narrow_eligible(v, cin, cout) || point_eligible<T>(v, cin, cout)) return launch_small<T, true>(X, W, v, cin, cout, Y, s);
+  if (narrow_eligible<T>(v, cin, cout) || point_eligible<T>(v, cin, cout)) return launch_small<T, true>(X, W, v, cin, cout, Y, s);
   if (rows_eligible<T>(v, cin, cout)) {
     if (v.n_out == 0) return SSCN_OK;
     if constexpr (sizeof(T) == 4) {
@@ -2996,7 +2995,7 @@ extern "C" sscn_status sparse_conv_backward(const void* features, const void* we
     const View vt = transposed_view(rb);
     if (dtype == SSCN_F32) {
       Heads<float> h = plain_heads((float*)dgrad, c_in);
-      if (narrow_eligible(vt, c_out, c_in) || point_eligible<float>(vt, c_out, c_in)) {
+      if (narrow_eligible<float>(vt, c_out, c_in) || point_eligible<float>(vt, c_out, c_in)) {
         st = launch_small<float, false>((const float*)dout, (const float*)weights, vt, c_out, c_in, h, stream);
       } else if (rows_eligible<float>(vt, c_out, c_in)) {
         if (wgrad) { h.zero = wgrad; h.n_zero = w_total; w_zeroed = true; }
@@ -3018,7 +3017,7 @@ extern "C" sscn_status sparse_conv_backward(const void* features, const void* we
       }
     } else {
       Heads<bf16_t> h = plain_heads((bf16_t*)dgrad, c_in);
-      if (narrow_eligible(vt, c_out, c_in) || point_eligible<bf16_t>(vt, c_out, c_in)) {
+      if (narrow_eligible<bf16_t>(vt, c_out, c_in) || point_eligible<bf16_t>(vt, c_out, c_in)) {
         st = launch_small<bf16_t, false>((const bf16_t*)dout, (const bf16_t*)weights, vt, c_out, c_in, h, stream);
       } else if (rows_eligible<bf16_t>(vt, c_out, c_in)) {
         if (wgrad) { h.zero = wgrad; h.n_zero = w_total; w_zeroed = true; }

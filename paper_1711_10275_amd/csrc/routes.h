@@ -76,4 +76,32 @@ inline bool point_is_faster(int elem_bytes, bool rows, int kdim, int ncols) {
   return kdim <= (groups >= 3 ? 24 : 16) * groups;
 }
 
+// Layers of kdim < 8 channels in and ncols out, K offsets: the narrow kernel
+// (k_conv_narrow) or what runs other layers, within 48 KB of LDS for the weights
+// and the tile's table (three workgroups a CU).
+//
+// The narrow kernel stages all weights for every 64 rows, whatever pairs the rows
+// have; the others pay per pair, in column groups of 64.  So the weights staged
+// (columns in whole fours) may be many where rows have many pairs, some where
+// rows have few, and more than that only in fp32, whose matrix products are the
+// dearer, when enough tiles hide the staging.  Measured us, narrow kernel against
+// the other:
+//   3x3x3, 11 pairs/row     4 -> 96 fp32   100k 144  285    7 -> 48 fp32  20k    48  189
+//   3x3x3, 1.1 pairs/row    6 -> 64 bf16   100k 102   64    6 -> 32 bf16  20k    23   57
+//   2x2x2 down              6 -> 96 bf16   20k   38   74    1 -> 512 bf16 20k    59   41
+//                           4 -> 192 fp32  20k   36   32    4 -> 192 fp32 100k   44   67
+//   2x2x2 up                7 -> 128 bf16  100k  74   46    5 -> 96 fp32  100k   36   63
+//   3x3x3x3, 4.6 pairs/row  4 -> 16 fp32   500k 315  158    4 -> 16 fp32  100k   79  104
+inline bool narrow_is_faster(int elem_bytes, int K, int kdim, int ncols, int64_t n_pairs, int64_t n_out) {
+  const int64_t weights = (int64_t)K * kdim * ((ncols + 3) / 4 * 4);
+  if (kdim >= 8 || 4 * weights + 256 * (int64_t)K > 48 * 1024) return false;
+  const double pairs = n_out > 0 ? (double)n_pairs / (double)n_out : 0.0;  // of a row
+  const int64_t tiles = (n_out + 63) / 64;
+  if (weights <= (K <= 27 ? 1000 : 400) * pairs) return true;
+  if (K > 27) return weights <= 6000 && tiles <= 2048;
+  if (weights <= 3500) return ncols <= 192 || tiles >= 400;
+  if (ncols <= 96 && weights <= 5400) return elem_bytes == 4 || kdim <= 6;
+  return elem_bytes == 4 && K <= 8 && tiles >= 400;
+}
+
 }  // namespace sscn

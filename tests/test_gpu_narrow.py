@@ -29,7 +29,7 @@ def _books(kind, f, s):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("kind,f,s,cin,cout", [
     ("ssc", 3, 1, 1, 32), ("ssc", 3, 1, 3, 33), ("ssc", 3, 1, 7, 4), ("ssc", 3, 1, 40, 2), ("ssc", 5, 1, 4, 5),
-    ("sc", 2, 2, 3, 16), ("sc", 3, 2, 6, 130), ("dc", 2, 2, 5, 8), ("ssc", 1, 1, 32, 32), ("ssc", 1, 1, 1, 1),
+    ("sc", 2, 2, 3, 16), ("sc", 3, 2, 6, 130), ("dc", 2, 2, 5, 8), ("dc", 2, 2, 7, 128), ("sc", 2, 2, 6, 96), ("ssc", 1, 1, 32, 32), ("ssc", 1, 1, 1, 1),
     ("ssc", 1, 1, 20, 51), ("ssc", 1, 1, 512, 2), ("ssc", 1, 1, 33, 32), ("ssc", 1, 1, 40, 20), ("ssc", 1, 1, 1, 1000),
     ("ssc", 1, 1, 32, 31), ("ssc", 1, 1, 70, 12), ("ssc", 1, 1, 70, 4), ("ssc", 1, 1, 44, 17), ("ssc", 1, 1, 60, 16)])
 def test_forward_dgrad(kind, f, s, cin, cout, dtype):

@@ -14,6 +14,9 @@ WRAP = """
 extern "C" int pool_table(int K, long long n_pairs, long long n_out, int pieces, int pb) {
   return sscn::pool_takes_table(K, n_pairs, n_out, (n_out + 63) / 64, pieces, pb);
 }
+extern "C" int narrow(int elem_bytes, int K, int kdim, int ncols, long long n_pairs, long long n_out) {
+  return sscn::narrow_is_faster(elem_bytes, K, kdim, ncols, n_pairs, n_out);
+}
 extern "C" int point(int elem_bytes, int kdim, int ncols) {
   return sscn::point_is_faster(elem_bytes, kdim % 8 == 0, kdim, ncols);
 }
@@ -28,6 +31,7 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "wrap.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
     lib.pool_table.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    lib.narrow.argtypes = [ctypes.c_int] * 4 + [ctypes.c_int64] * 2
     return lib
 
 
@@ -107,3 +111,37 @@ def test_per_site_rule_takes_the_faster_kernel(rules):
     # fp32 rows taken as bf16 parts keep their rounding
     assert not any(rules.point(4, kdim, 4) for kdim in (16, 24, 32, 40, 64, 128))
     assert not rules.point(4, 65536, 65536)  # the product of the largest widths stays in range
+
+
+# offsets, pairs, rows written, reduction channels, columns, dtype, us of the narrow kernel, us of the general kernels
+NARROW = [
+    (27, 1140000, 100000, 3, 32, "f32", 27.9, 204.6), (27, 1140000, 100000, 4, 96, "f32", 143.7, 285.4),
+    (27, 220000, 20000, 7, 48, "f32", 48.0, 188.7), (27, 19000, 1799, 3, 32, "bf16", 24.7, 157.5),
+    (27, 5700000, 500000, 4, 96, "bf16", 776.6, 1014.7), (27, 110303, 100000, 6, 64, "bf16", 102.3, 64.5),
+    (27, 22080, 20000, 6, 32, "bf16", 23.0, 56.8), (27, 604300, 500000, 3, 128, "bf16", 468.6, 346.9),
+    (27, 1959, 1799, 4, 96, "f32", 37.5, 25.3), (125, 1500000, 50000, 4, 8, "f32", 69.5, 177.7),
+    (8, 20000, 6140, 6, 96, "bf16", 38.2, 73.6), (8, 20000, 6140, 1, 512, "bf16", 59.0, 41.2),
+    (8, 20000, 6140, 4, 192, "f32", 36.5, 32.1), (8, 100000, 25821, 4, 192, "f32", 43.7, 67.2),
+    (8, 500000, 136670, 5, 160, "f32", 129.2, 280.6), (8, 100000, 100000, 7, 128, "bf16", 73.5, 46.0),
+    (8, 100000, 100000, 5, 96, "f32", 35.5, 63.5), (8, 1799, 1799, 1, 256, "bf16", 25.8, 21.7),
+    (8, 1799, 1799, 4, 256, "f32", 36.3, 22.6), (8, 500000, 500000, 7, 96, "bf16", 186.1, 182.9),
+    (8, 500000, 500000, 7, 96, "f32", 153.5, 206.6), (81, 2307196, 500000, 4, 16, "f32", 314.5, 158.3),
+    (81, 457088, 100000, 4, 16, "f32", 79.1, 104.0), (81, 2307196, 500000, 1, 16, "f32", 118.8, 245.7),
+    (81, 2307196, 500000, 5, 12, "bf16", 394.7, 228.7),
+]
+
+
+def test_narrow_rule_takes_the_faster_kernel(rules):
+    for K, n_pairs, n_out, kdim, ncols, dtype, here, general in NARROW:
+        got = bool(rules.narrow(4 if dtype == "f32" else 2, K, kdim, ncols, n_pairs, n_out))
+        assert got == (here < general), (K, n_out, kdim, ncols, dtype)
+
+
+def test_narrow_rule_keeps_within_the_lds(rules):
+    """No more than 48 KB of weights and table, whatever the pairs."""
+    for K in (1, 8, 27, 125, 512):
+        for kdim in range(1, 8):
+            for ncols in (1, 4, 5, 64, 300, 3000, 65536):
+                if rules.narrow(4, K, kdim, ncols, K * 10 ** 6, 10 ** 6):
+                    assert 4 * K * kdim * -(-ncols // 4) * 4 + 256 * K <= 48 * 1024
+    assert not rules.narrow(4, 27, 8, 4, 10 ** 7, 10 ** 6) and not rules.narrow(4, 27, 7, 65536, 10 ** 7, 10 ** 6)
