@@ -1705,47 +1705,6 @@ __global__ void k_plan_items(const uint32_t* __restrict__ bmask, int W, const in
   }
 }
 
-// The same with the items' input rows, for an SSC build that still holds its
-// neighbour map (nbr[o n + k]: the input row of output row k through offset o,
-// -1 for none): a wavefront writes its block's items whole, eight reads of the
-// map in flight per lane, in place of the marks of k_plan_items and a walk over
-// all pairs that scatters 4 bytes each (k_plan_pairs).  Bound by its scattered
-// 4-byte reads.  1.96M sites: 153 us (159 and the marks before; SSC(3) and
-// SC(2,2) books with export 1158 -> 1134 us; consecutive blocks on one XCD:
-// 1217 us).  Only from kMirrorProbeMin sites on: at 99,515 the chain of reads
-// is longer than the two launches (layer step 367 -> 374 us).
-__global__ __launch_bounds__(256) void k_plan_gather(const uint32_t* __restrict__ bmask, int W,
-                                                     const int32_t* __restrict__ b_first, int64_t n_blocks,
-                                                     const int32_t* __restrict__ perm, const int32_t* __restrict__ nbr,
-                                                     int64_t n, uint32_t* __restrict__ items) {
-  const int64_t b =
-      (int64_t)blockIdx.x * (blockDim.x / kPlanRows) + __builtin_amdgcn_readfirstlane(threadIdx.x / kPlanRows);
-  const int m = threadIdx.x % kPlanRows;
-  if (b >= n_blocks) return;
-  const int32_t r = perm[b * kPlanRows + m];  // -1 past the last row
-  uint32_t* dst = items + (int64_t)b_first[b] * kPlanRows + m;
-  for (int i = 0; i < W; ++i) {
-    uint32_t u = bmask[b * W + i];
-    while (u) {  // uniform
-      constexpr int U = 8;
-      int o[U];
-      int32_t j[U];
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        o[q] = u ? 32 * i + __ffs(u) - 1 : -1;
-        u &= u - 1;  // 0 stays 0
-        j[q] = o[q] >= 0 && r >= 0 ? nbr[(int64_t)o[q] * n + r] : -1;
-      }
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        if (o[q] < 0) break;
-        *dst = (j[q] >= 0 ? (uint32_t)j[q] : (uint32_t)kPlanNoRow) | ((uint32_t)o[q] << kPlanRowBits);
-        dst += kPlanRows;
-      }
-    }
-  }
-}
-
 // Every pair into its block's item for its offset, at its row's slot.
 __global__ void k_plan_pairs(const int64_t* __restrict__ seg, int64_t n_tiles, const int32_t* __restrict__ in_rows,
                              const int32_t* __restrict__ out_rows, const int32_t* __restrict__ pos_of,
@@ -1948,7 +1907,7 @@ static KeySel plan_key_sel(int K, int f, int dim) {
 }
 
 static sscn_status build_plan(RulebookData* d, Storage& st, int64_t n_rows, int K, hipStream_t s,
-                              int64_t ppo_bound = -1, int32_t* hist0 = nullptr, const int32_t* nbr = nullptr) {
+                              int64_t ppo_bound = -1, int32_t* hist0 = nullptr) {
   const int64_t nb = ceil_div(n_rows, kPlanRows);
   st.n_blocks = nb;
   const int64_t cap =
@@ -2011,11 +1970,6 @@ static sscn_status build_plan(RulebookData* d, Storage& st, int64_t n_rows, int 
     k_order_place<<<owgs, 256, 0, s>>>(st.b_first, nb, K, ohist, ohist + kOrderBins, st.b_rec);
   }
   SSCN_HIP(hipGetLastError());
-  if (nbr) {
-    k_plan_gather<<<grid_for(nb * kPlanRows, 256), 256, 0, s>>>(bmask, W, st.b_first, nb, st.perm, nbr, n_rows, st.items);
-    SSCN_HIP(hipGetLastError());
-    return SSCN_OK;
-  }
   k_plan_items<<<grid_for(nb * kPlanRows, 256), 256, 0, s>>>(bmask, W, st.b_first, nb, st.items);
   SSCN_HIP(hipGetLastError());
   if (max_ppo > 0) {
@@ -2208,8 +2162,7 @@ static sscn_status ssc_build(const int32_t* coords, int64_t n, const int32_t* sp
     // while it returns (a use of the plan on another stream waits for the
     // rule book's stream).
     SSCN_TRY(readback_begin(direct ? nullptr : stats, stat_bytes, s));
-    if (eager_plan) SSCN_TRY(build_plan(d, d->fwd, n, K, s, /*a site has one neighbour per offset*/ n, hist,
-                                       n >= kMirrorProbeMin ? nbr : nullptr));
+    if (eager_plan) SSCN_TRY(build_plan(d, d->fwd, n, K, s, /*a site has one neighbour per offset*/ n, hist));
     std::vector<unsigned long long> host(1 + K);
     SSCN_TRY(readback_end(host.data(), stat_bytes));
     if (!(host[0] & kFlagOutOfRange) && (host[0] & kFlagWideKey)) {

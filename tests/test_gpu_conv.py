@@ -445,11 +445,19 @@ def test_filter1_per_row(cin, cout, dtype):
 @pytest.mark.parametrize("n", [1 << 18, (1 << 18) + 65])
 @pytest.mark.parametrize("f", [1, 3])
 def test_ssc_plan_from_the_neighbour_map(n, f):
-    """The plan an SSC build of 2^18 sites or more writes from its neighbour
-    map: the smallest such build, and one with a part block."""
+    """The plan that an SSC build of 2^18 sites or more makes beside its mirrored
+    neighbour map: the smallest such build, and one with a part block; an fp32
+    layer both ways, and a bf16 layer whose wgrad walks the plan's blocks."""
     size = (60, 60, 62)
     coords = small_set(600, size, batch=2, density=0.6)[:n]
     assert coords.shape[0] == n
     rb, orb = sscn.ssc_rulebook_build(dev(coords), size, f), O.ssc_rulebook(coords, size, f)
     X, W = _draw(n, 24, 48, f ** 3, 601, "f32")
     assert_close(_fwd(rb, X, W, "f32"), O.forward(X, W, orb), "f32", "forward")
+    for dtype, cin, cout in (("f32", 24, 48), ("bf16", 32, 32)):
+        X, W = _draw(n, cin, cout, f ** 3, 602, dtype)
+        G = S.features(n, cout, 603, bf16=dtype == "bf16")
+        dx, dw = sscn.sparse_conv_backward(dev(X, TD[dtype]), dev(W, TD[dtype]), dev(G, TD[dtype]), rb)
+        rdx, rdw = O.backward(X, W, G, orb)
+        assert_close(host(dx), rdx, dtype, "dgrad")
+        assert_close(host(dw), rdw, "f32", "wgrad")
