@@ -488,7 +488,13 @@ static sscn_status launch_small(const T* X, const T* W, const View& v, int kdim,
       }
       return pieces ? k_conv_point<T, TR, V, 0> : k_conv_point<T, TR, 1, 0>;
     }();
-    kern<<<(unsigned)ceil_div(v.n_out, rows), 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
+    const dim3 grid((unsigned)ceil_div(v.n_out, rows));
+    hipEvent_t t0, t1;
+    // in the row-block kernel's place: its launch timer too
+    if (rows_eligible<T>(v, kdim, ncols) && take_launch_timer(&t0, &t1))
+      hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds, s, t0, t1, 0, X, W, kdim, ncols, v.n_out, rows, Y);
+    else
+      kern<<<grid, 256, lds, s>>>(X, W, kdim, ncols, v.n_out, rows, Y);
     SSCN_HIP(hipGetLastError());
     return SSCN_OK;
   }

@@ -89,6 +89,26 @@ def test_kernel_timer_brackets_the_row_kernel():
     assert t.ms() == kernel_ms
 
 
+@pytest.mark.parametrize("dtype,cin,cout", [(torch.bfloat16, 32, 20), (torch.float32, 8, 6), (torch.float32, 32, 20)])
+def test_kernel_timer_brackets_a_per_site_layer(dtype, cin, cout):
+    """The same of a filter-size-1 layer, whether the row-block kernel runs it or
+    the per-site kernel in its place: the forward takes the request, and a wgrad
+    after it finds none."""
+    coords, size = coords_for("shell32")
+    rb = sscn.ssc_rulebook_build(dev(coords), size, 1)
+    n = coords.shape[0]
+    X, W, G = (dev(a, dtype) for a in (S.features(n, cin, 97), S.weights(1, cin, cout, 98), S.features(n, cout, 99)))
+    t = sscn.KernelTimer()
+    t.arm()
+    sscn.sparse_conv_forward(X, W, rb)
+    torch.cuda.synchronize()
+    kernel_ms = t.ms()
+    assert kernel_ms > 0.0
+    sscn.sparse_conv_backward(X, W, G, rb, dgrad=False)
+    torch.cuda.synchronize()
+    assert t.ms() == kernel_ms
+
+
 def test_device_memory_cap_gives_oom_and_recovers():
     """A cap on the library's device memory below what a build needs makes
     the build fail with the out-of-memory status (after the idle blocks are
