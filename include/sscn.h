@@ -478,8 +478,9 @@ sscn_status sscn_sgd_nesterov(float* params, const float* grads, float* momentum
 
 /*
  * sscn_sgd_nesterov_many -- sscn_sgd_nesterov on n_tensors parameter tensors
- * (a host array of their pointers and counts, read before the call returns)
- * in as few launches as hold them.  No two tensors may overlap.
+ * one after another (a host array of their pointers and counts, read before
+ * the call returns), in as few launches as hold them: a tensor that shares
+ * memory with an earlier one of its launch starts the next.
  */
 typedef struct {
   float* params;

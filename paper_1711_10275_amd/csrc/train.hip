@@ -16,6 +16,7 @@
 
 #include "internal.h"
 #include "numeric.h"
+#include "sgd_batch.h"
 
 namespace sscn {
 
@@ -597,12 +598,10 @@ __global__ void k_sgd_nesterov(float* __restrict__ p, const float* __restrict__ 
   }
 }
 // Up to kSgdTensors tensors in one launch, their table in the kernel's
-// arguments (2.8 KB of the 4 that those may have): workgroup b takes 1024
-// elements of the tensor whose range of workgroups, [first[k], first[k + 1]),
-// holds b.  A network's parameters are many small tensors (46 of them, 8 to
-// 7k elements, in a three-level network of 8 channels), whose update is all
-// launches, not bytes.
-constexpr int kSgdTensors = 64, kSgdPer = 1024;
+// arguments: workgroup b takes kSgdPer elements of the tensor whose range of
+// workgroups, [first[k], first[k + 1]), holds b.  A network's parameters are
+// many small tensors (46 of them, 8 to 7k elements, in a three-level network of
+// 8 channels), whose update is all launches, not bytes.
 struct SgdTable {
   sscn_sgd_tensor t[kSgdTensors];
   uint32_t first[kSgdTensors + 1];
@@ -882,28 +881,27 @@ extern "C" sscn_status sscn_sgd_nesterov_many(const sscn_sgd_tensor* tensors, in
     if (t.count > 0 && (!t.params || !t.grads || !t.momentum_buf))
       return fail(SSCN_ERR_INVALID_ARG, "NULL params, grads or momentum buffer");
   }
-  SgdTable tab;
-  tab.n = 0;
-  tab.first[0] = 0;
-  const auto flush = [&]() -> sscn_status {
-    if (tab.n == 0) return SSCN_OK;
+  for (int32_t k = 0; k < n_tensors;) {
+    const int32_t end = k + sgd_batch(tensors + k, n_tensors - k);
+    SgdTable tab;
+    tab.n = 0;
+    tab.first[0] = 0;
+    for (; k < end; ++k) {
+      const sscn_sgd_tensor& t = tensors[k];
+      if (t.count == 0) continue;
+      const int64_t groups = sgd_groups(t.count);
+      if (groups > (1 << 20)) {  // 1G elements: a launch of its own, over a bounded grid
+        SSCN_TRY(sscn_sgd_nesterov(t.params, t.grads, t.momentum_buf, t.count, lr, momentum, weight_decay,
+                                   t.params_bf16, stream));
+        continue;
+      }
+      tab.t[tab.n] = t;
+      tab.first[tab.n + 1] = tab.first[tab.n] + (uint32_t)groups;
+      ++tab.n;
+    }
+    if (tab.n == 0) continue;
     k_sgd_nesterov_many<<<tab.first[tab.n], 256, 0, stream>>>(tab, lr, momentum, weight_decay);
     SSCN_HIP(hipGetLastError());
-    tab.n = 0;
-    return SSCN_OK;
-  };
-  for (int32_t k = 0; k < n_tensors; ++k) {
-    const sscn_sgd_tensor& t = tensors[k];
-    if (t.count == 0) continue;
-    const int64_t groups = ceil_div(t.count, (int64_t)kSgdPer);
-    if (groups > (1 << 20)) {  // 1G elements: a launch of its own, over a bounded grid
-      SSCN_TRY(sscn_sgd_nesterov(t.params, t.grads, t.momentum_buf, t.count, lr, momentum, weight_decay, t.params_bf16,
-                                 stream));
-      continue;
-    }
-    tab.t[tab.n] = t;
-    tab.first[tab.n + 1] = tab.first[tab.n] + (uint32_t)groups;
-    if (++tab.n == kSgdTensors) SSCN_TRY(flush());
   }
-  return flush();
+  return SSCN_OK;
 }

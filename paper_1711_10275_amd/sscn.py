@@ -633,15 +633,14 @@ def sgd_nesterov_(params, grads, buf, lr, momentum=0.9, weight_decay=1e-4, param
 
 def sgd_nesterov_many_(items, lr, momentum=0.9, weight_decay=1e-4):
     """sgd_nesterov_ on every (params, grads, buf, bf16 copy or None) of
-    `items` in one call; one after another where two of them share memory's
-    start or they are not all on one device."""
+    `items`, one after another, in one call (a call each where they are not
+    all on one device)."""
     for it in items:
         _check_sgd(*it)
     if not items:
         return
     dev = items[0][0].device
-    starts = [t.data_ptr() for p, _, b, c in items for t in (p, b, c) if t is not None and t.numel()]
-    if len(set(starts)) < len(starts) or any(t.device != dev for it in items for t in it if t is not None):
+    if any(t.device != dev for it in items for t in it if t is not None):
         for p, g, b, c in items:
             sgd_nesterov_(p, g, b, lr, momentum, weight_decay, params_bf16=c)
         return

@@ -113,6 +113,24 @@ def test_sgd_nesterov_many_equals_one_by_one():
                 assert t is None or torch.equal(t, want[id(t)])
 
 
+def test_sgd_nesterov_many_on_shared_memory():
+    """Views that partly overlap, and a gradient that is another tensor's
+    parameters: as one after another."""
+    rng = np.random.default_rng(9)
+    base = dev(rng.standard_normal(5000).astype(np.float32))
+    own = [dev(rng.standard_normal(3000).astype(np.float32)) for _ in range(8)]
+
+    def items(p, t):
+        return [(p[:3000], t[0], t[1], None), (p[1500:4500], t[2], t[3], None), (t[4], p[2000:], t[5], None),
+                (t[6], t[4], t[7], None)]
+
+    want = (base.clone(), [t.clone() for t in own])
+    for q in items(*want):
+        sscn.sgd_nesterov_(q[0], q[1], q[2], 0.1, params_bf16=q[3])
+    sscn.sgd_nesterov_many_(items(base, own), 0.1)
+    assert torch.equal(base, want[0]) and all(torch.equal(a, b) for a, b in zip(own, want[1]))
+
+
 def test_sgd_nesterov_two_steps():
     rng = np.random.default_rng(6)
     p0 = rng.standard_normal(1001).astype(np.float32)
