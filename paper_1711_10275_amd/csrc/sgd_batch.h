@@ -12,12 +12,16 @@ namespace sscn {
 constexpr int kSgdTensors = 64;
 // Elements of a tensor per workgroup.
 constexpr int kSgdPer = 1024;
+// Workgroups of one launch (1G elements; a grid may have 2^32 threads, 2^24
+// workgroups).  A tensor of more goes alone.
+constexpr int64_t kSgdGroups = 1 << 20;
 
 inline int64_t sgd_groups(int64_t count) { return (count + kSgdPer - 1) / kSgdPer; }
 
 // The number of leading tensors (n >= 1 of them, empty ones included) that one
-// launch updates as if one after another: at most kSgdTensors, and none that
-// shares memory with an earlier one, unless both only read there.
+// launch updates as if one after another: at most kSgdTensors of kSgdGroups
+// workgroups in all, and none that shares memory with an earlier one, unless
+// both only read there.
 template <class Tensor>
 int sgd_batch(const Tensor* t, int n) {
   struct Range {
@@ -27,12 +31,15 @@ int sgd_batch(const Tensor* t, int n) {
   };
   Range r[4 * kSgdTensors];
   int ranges = 0, taken = 0, k = 0;
+  int64_t groups = 0;
   const auto add = [&](const void* p, int64_t bytes, bool written) {
     const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
     r[ranges++] = Range{lo, lo + (uintptr_t)bytes, written, k};
   };
   for (; k < n && taken < kSgdTensors; ++k) {
     if (t[k].count == 0) continue;
+    groups += sgd_groups(t[k].count);
+    if (taken > 0 && groups > kSgdGroups) break;
     ++taken;
     add(t[k].params, 4 * t[k].count, true);
     add(t[k].grads, 4 * t[k].count, false);

@@ -890,7 +890,7 @@ extern "C" sscn_status sscn_sgd_nesterov_many(const sscn_sgd_tensor* tensors, in
       const sscn_sgd_tensor& t = tensors[k];
       if (t.count == 0) continue;
       const int64_t groups = sgd_groups(t.count);
-      if (groups > (1 << 20)) {  // 1G elements: a launch of its own, over a bounded grid
+      if (groups > kSgdGroups) {  // alone, over a bounded grid
         SSCN_TRY(sscn_sgd_nesterov(t.params, t.grads, t.momentum_buf, t.count, lr, momentum, weight_decay,
                                    t.params_bf16, stream));
         continue;

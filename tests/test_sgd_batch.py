@@ -92,3 +92,20 @@ def test_against_pairs(launches):
         for x, y in zip(got, got[1:]):  # no launch ends early
             full = sum(1 for i in x if ts[i][4]) == 64
             assert full or any(_meet(ts[i], ts[y[0]]) for i in x if ts[i][4])
+
+
+def test_a_launch_stays_within_its_grid(launches):
+    """A launch's workgroups of 256 threads stay far below the 2^32 threads that a
+    grid may have, and 32-bit numbers hold them; a tensor of more is alone."""
+    def groups(i, ts):
+        return -(-ts[i][4] // 1024)
+
+    big = [((3 * i + 1) << 36, (3 * i + 2) << 36, (3 * i + 3) << 36, None, 1 << 30) for i in range(17)]
+    mixed = [(*t[:4], n) for t, n in zip(big, [5, (1 << 30) + 1, 7, 1 << 29, 1 << 29, 1, (1 << 33), 1 << 20, 3])]
+    for ts in (big, mixed):
+        got = launches(ts)
+        assert [i for x in got for i in x] == list(range(len(ts)))
+        for x in got:
+            assert len(x) == 1 or sum(groups(i, ts) for i in x) <= 1 << 20
+    assert len(launches(big)) == 17
+    assert launches(mixed) == [[0], [1], [2, 3], [4, 5], [6], [7, 8]]
