@@ -24,24 +24,26 @@ namespace sscn {
 //   27    1       36 fp32, 100k      24.1   19.1      96
 //   64    1       64 fp32, 1M         297    264     128
 //   64    1       13 fp32, 2k        23.8   18.9     315
-//   125   1       64 fp32, 100k      98.2   59.1     250
 //   64    1        5 fp32, 1M         136    253     205
+//   125   1       64 fp32, 100k      98.2   59.1     250
 //   216   1       64 fp32, 100k       359   92.2     432
 //   512   1       64 fp32, 100k      1528    196    1024
 //   512   61      64 fp32, 100k       177    647      17    average
+//   256   5        8 bf16, 400k       230    173      51    average, 4-d
 // Threads of 8 rows and more (single channels of rows of 17 and more) lose to
 // the walk where few tiles leave their chain of rows bare (27 offsets, 100 bf16
-// channels, 2k sites: average 48.6 against 31.4); beyond 512 workgroups and at a
-// pair per 5 offsets the chip is full and they win (33 fp32 channels, 500k:
-// 61 against 129).
+// channels, 2k sites: average 48.6 against 31.4); beyond 512 workgroups (1024 of
+// few offsets), with several pairs a row and one per 5 offsets, the chip is full
+// and they win (27 offsets, 33 fp32 channels, 500k: 61 against 129; 4 offsets,
+// one pair, 33 bf16, 100k: 15.6 against 12.5).
 inline bool pool_takes_table(int K, int64_t n_pairs, int64_t n_out, int64_t tiles, int pieces, int pb) {
   const int64_t groups = (pieces + (1 << pb) - 1) >> pb;
   const double pairs = n_out > 0 ? (double)n_pairs / (double)n_out : 0.0;  // of a row
-  if (K <= 5 * pairs && tiles * groups >= 512) return true;
+  if (pairs >= 3 && K <= 5 * pairs && tiles * groups >= (K < 16 ? 1024 : 512)) return true;
   if (pb > (K <= 27 ? 5 : 4)) return false;
   const double rows = pb > 2 ? (double)(1 << pb) / 4 : 1.0, idle = (double)(groups << pb) / pieces;
   const double lookups = K * rows * idle;
-  const int most = groups > 1 || K > 128 ? 64 : K <= 64 && pb <= 4 && tiles >= 2048 ? 270 : 90;
+  const int most = K > 128 ? 30 : groups > 1 ? 64 : K <= 64 && pb <= 4 && tiles >= 2048 ? 270 : 90;
   return lookups <= most * pairs;
 }
 

@@ -84,6 +84,13 @@ def test_pool_rule_takes_the_faster_kernel(rules):
         assert got == (table < walk), (f, n_out, n_pairs, c, dtype)
 
 
+def test_pool_rule_in_other_dimensions(rules):
+    """Offsets, pairs and rows of 2- and 4-d fields."""
+    for K, n_out, n_pairs, c, dtype, table, walk in [(4, 100000, 100000, 33, "bf16", 15.6, 12.5), (9, 100000, 223000, 33, "bf16", 28.3, 22.1),
+                                                     (256, 79000, 400000, 8, "bf16", 229.7, 173.3)]:
+        assert bool(rules.pool_table(K, n_pairs, n_out, *_pieces(c, dtype))) == (table < walk), (K, n_out, c)
+
+
 def test_pool_rule_at_its_ends(rules):
     assert not rules.pool_table(8, 0, 100, *_pieces(64, "f32"))  # no pairs: nothing to look up
     assert not rules.pool_table(8, 0, 0, *_pieces(1, "f32"))
