@@ -90,6 +90,7 @@ inline bool point_is_faster(int elem_bytes, bool rows, int kdim, int ncols) {
 // the other:
 //   3x3x3, 11 pairs/row     4 -> 96 fp32   100k 144  285    7 -> 48 fp32  20k    48  189
 //   3x3x3, 1.1 pairs/row    6 -> 64 bf16   100k 102   64    6 -> 32 bf16  20k    23   57
+//     rows in random order  7 -> 48 bf16   500k 1144  694    7 -> 48 fp32  500k  555  776
 //   2x2x2 down              6 -> 96 bf16   20k   38   74    1 -> 512 bf16 20k    59   41
 //                           4 -> 192 fp32  20k   36   32    4 -> 192 fp32 100k   44   67
 //   2x2x2 up                7 -> 128 bf16  100k  74   46    5 -> 96 fp32  100k   36   63
@@ -99,9 +100,9 @@ inline bool narrow_is_faster(int elem_bytes, int K, int kdim, int ncols, int64_t
   if (kdim >= 8 || 4 * weights + 256 * (int64_t)K > 48 * 1024) return false;
   const double pairs = n_out > 0 ? (double)n_pairs / (double)n_out : 0.0;  // of a row
   const int64_t tiles = (n_out + 63) / 64;
-  if (weights <= (K <= 27 ? 1000 : 400) * pairs) return true;
+  if (weights <= (K > 27 ? 400 : elem_bytes == 4 ? 1000 : 600) * pairs) return true;
   if (K > 27) return weights <= 6000 && tiles <= 2048;
-  if (weights <= 3500) return ncols <= 192 || tiles >= 400;
+  if (weights <= (elem_bytes == 2 && kdim == 7 ? 2000 : 3500)) return ncols <= 192 || tiles >= 400;
   if (ncols <= 96 && weights <= 5400) return elem_bytes == 4 || kdim <= 6;
   return elem_bytes == 4 && K <= 8 && tiles >= 400;
 }

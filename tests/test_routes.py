@@ -124,14 +124,14 @@ def test_per_site_rule_takes_the_faster_kernel(rules):
 NARROW = [
     (27, 1140000, 100000, 3, 32, "f32", 27.9, 204.6), (27, 1140000, 100000, 4, 96, "f32", 143.7, 285.4),
     (27, 220000, 20000, 7, 48, "f32", 48.0, 188.7), (27, 19000, 1799, 3, 32, "bf16", 24.7, 157.5),
-    (27, 5700000, 500000, 4, 96, "bf16", 776.6, 1014.7), (27, 110303, 100000, 6, 64, "bf16", 102.3, 64.5),
+    (27, 5700000, 500000, 7, 48, "bf16", 1143.8, 694.1), (27, 110303, 100000, 6, 64, "bf16", 102.3, 64.5),
     (27, 22080, 20000, 6, 32, "bf16", 23.0, 56.8), (27, 604300, 500000, 3, 128, "bf16", 468.6, 346.9),
     (27, 1959, 1799, 4, 96, "f32", 37.5, 25.3), (125, 1500000, 50000, 4, 8, "f32", 69.5, 177.7),
     (8, 20000, 6140, 6, 96, "bf16", 38.2, 73.6), (8, 20000, 6140, 1, 512, "bf16", 59.0, 41.2),
     (8, 20000, 6140, 4, 192, "f32", 36.5, 32.1), (8, 100000, 25821, 4, 192, "f32", 43.7, 67.2),
     (8, 500000, 136670, 5, 160, "f32", 129.2, 280.6), (8, 100000, 100000, 7, 128, "bf16", 73.5, 46.0),
     (8, 100000, 100000, 5, 96, "f32", 35.5, 63.5), (8, 1799, 1799, 1, 256, "bf16", 25.8, 21.7),
-    (8, 1799, 1799, 4, 256, "f32", 36.3, 22.6), (8, 500000, 500000, 7, 96, "bf16", 186.1, 182.9),
+    (8, 500000, 500000, 7, 48, "bf16", 139.4, 123.3), (8, 1799, 1799, 4, 256, "f32", 36.3, 22.6), (8, 500000, 500000, 7, 96, "bf16", 186.1, 182.9),
     (8, 500000, 500000, 7, 96, "f32", 153.5, 206.6), (81, 2307196, 500000, 4, 16, "f32", 314.5, 158.3),
     (81, 457088, 100000, 4, 16, "f32", 79.1, 104.0), (81, 2307196, 500000, 1, 16, "f32", 118.8, 245.7),
     (81, 2307196, 500000, 5, 12, "bf16", 394.7, 228.7),
