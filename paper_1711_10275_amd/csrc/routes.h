@@ -21,7 +21,8 @@ namespace sscn {
 //   K  pairs/row  channels          table   walk   lookups
 //   8     3.9     64 fp32, 100k       9.9   38.2       4    average
 //   27    1       16 fp32, 100k      10.6   18.6      27    its gradient
-//   27    1       36 fp32, 100k      24.1   19.1      96
+//   27    1       36 fp32, 100k      24.1   19.1      96    two column groups
+//   27    1       13 bf16, 20k       13.7   14.3     133
 //   64    1       64 fp32, 1M         297    264     128
 //   64    1       13 fp32, 2k        23.8   18.9     315
 //   64    1        5 fp32, 1M         136    253     205
@@ -43,7 +44,7 @@ inline bool pool_takes_table(int K, int64_t n_pairs, int64_t n_out, int64_t tile
   if (pb > (K <= 27 ? 5 : 4)) return false;
   const double rows = pb > 2 ? (double)(1 << pb) / 4 : 1.0, idle = (double)(groups << pb) / pieces;
   const double lookups = K * rows * idle;
-  const int most = K > 128 ? 30 : groups > 1 ? 64 : K <= 64 && pb <= 4 && tiles >= 2048 ? 270 : 90;
+  const int most = K > 128 ? 30 : groups > 1 ? 64 : pb > 4 || K > 64 ? 90 : tiles >= 2048 ? 270 : K <= 27 ? 140 : 90;
   return lookups <= most * pairs;
 }
 

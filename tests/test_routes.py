@@ -52,6 +52,7 @@ POOL = [
     (3, 100000, 100000, 16, "f32", 10.6, 18.6),  # its gradient
     (3, 100000, 100000, 36, "f32", 24.1, 19.1),  # its gradient
     (3, 32426, 275876, 32, "bf16", 10.5, 43.9),  # average
+    (3, 20000, 20000, 13, "bf16", 13.7, 14.3),  # its gradient
     (4, 71432, 1000000, 64, "f32", 72.1, 303.1),  # average
     (4, 1000000, 1000000, 64, "f32", 296.7, 264.1),  # its gradient
     (4, 1000000, 1000000, 5, "f32", 135.9, 252.5),  # its gradient
