@@ -250,10 +250,11 @@ __device__ __forceinline__ void stage_weights(const T* __restrict__ W, int K, in
 // LDS table (input row by offset and output row, -1 for none), and a thread
 // sums 4 columns of an output row over the offsets in order with fp32
 // multiply-adds, the rows of four offsets in flight.  Bound by instruction
-// issue (about 27 x (3 + 12) loads and multiply-adds a thread at 3 channels).
-// 99,515 sites, 1.14M pairs, 3 -> 32 channels, fp32: 32 us; 251 us on the
-// generic kernel, which walks the tile's pairs 16 at a time through a
-// 64-channel window.
+// issue: at 3 -> 32 channels a thread stages 10 weights, each with a few
+// divisions by run-time widths, and runs 2 x 27 offsets of 3 loads and 12
+// multiply-adds where there is a pair.  99,515 sites, 1.14M pairs, fp32: 33 us;
+// 251 us on the generic kernel, which walks the tile's pairs 16 at a time
+// through a 64-channel window.
 template <typename T, int CI, bool TR>
 __global__ __launch_bounds__(256) void k_conv_narrow(const T* __restrict__ X, const T* __restrict__ W,
                                                      const int64_t* __restrict__ seg, int64_t n_tiles,

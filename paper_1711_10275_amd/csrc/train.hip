@@ -514,7 +514,7 @@ __global__ __launch_bounds__(256) void k_softmax_nll(const T* __restrict__ z, in
 // The same for at most kSoftmaxRowMax classes, one thread per row: a
 // wavefront then reads 64 consecutive rows (one wavefront per row left most
 // lanes idle and took 1.1 ms for 2M rows of 20 classes).  The row losses
-// are added per thread, then per workgroup in thread order.
+// are added per thread, then over the workgroup in a fixed tree.
 constexpr int kSoftmaxRowMax = 64;
 template <typename T>
 __global__ __launch_bounds__(256) void k_softmax_nll_rows(const T* __restrict__ z, int64_t n, int classes, int ldl,
@@ -523,8 +523,7 @@ __global__ __launch_bounds__(256) void k_softmax_nll_rows(const T* __restrict__ 
   // The workgroup's 256 rows go through LDS (fp32, ldl values apart), loaded
   // and stored as the consecutive values that they are; a lane on its own row
   // of global memory touched a line per value (27 us at 99,515 x 20 fp32,
-  // half of it the serial sum of the 256 row losses; now
-  // 16 us).
+  // half of it the serial sum of the 256 row losses; now 15 us).
   extern __shared__ float rows[];
   __shared__ double red[4];
   const float inv_n = 1.f / (float)n;
